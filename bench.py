@@ -65,7 +65,7 @@ PAPER_DECODE_MS = {"decode_llama3_8b_h32kv8_cache4096": 0.034, "decode_llama3_70
 # The paper's block-sparse forward latency (BigBird mask, N = 4096), other hardware: context only.
 PAPER_SPARSE_MS = {"bigbird_b4h12s4096d64": 0.084}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "fwd_llama3_8b_hbm_traffic.json")
-FWD_SOURCES = ("fwd_bf16.hip", "attn_tiles.hpp", "common.hpp")
+FWD_SOURCES = ("fwd_kernel.hpp", "fwd_prerot.hip", "rope.hip", "attn_tiles.hpp", "common.hpp")
 
 
 def fwd_source_hash():

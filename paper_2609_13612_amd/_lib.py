@@ -39,6 +39,13 @@ SIGNATURES = {
     "attnfuse_version": (_I, []),
 }
 
+# Symbols of csrc/binding.h, which only this package calls.
+BINDING_SIGNATURES = {
+    "af_fwd_workspace_bytes": (ctypes.c_size_t, [_I, _I, _I, _I, _I, _I, _I, _I, _I, _L]),
+    "af_fwd_ws": (_I, [_P, _P, _P, _P, _P, _P, _P, _P, _L, _L, _L, _I, _P, ctypes.c_size_t,
+                       _I, _I, _I, _I, _I, _I, _I, _F, _P, _I, _I, _I, _P, _F, _P]),
+}
+
 _lib = None
 
 
@@ -51,7 +58,7 @@ def load():
                 f"{LIB_PATH} is missing: build it with `python -m paper_2609_13612_amd.build` "
                 "(there is no non-HIP fallback)")
         lib = ctypes.CDLL(LIB_PATH)
-        for name, (res, args) in SIGNATURES.items():
+        for name, (res, args) in {**SIGNATURES, **BINDING_SIGNATURES}.items():
             fn = getattr(lib, name)
             fn.restype = res
             fn.argtypes = args

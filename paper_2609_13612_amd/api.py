@@ -5,6 +5,7 @@ shape/dtype/contiguity against the call, passes raw device pointers and the
 current torch stream to the library, and raises AttnFuseError on a non-zero
 return code.  Every step of the computation runs in the HIP kernels.
 """
+import functools
 import math
 
 import numpy as np
@@ -175,6 +176,25 @@ def _variant(rope, theta, mask, window, alibi_slopes, scale, D, H=None, device=N
     return ROPE[rope], float(theta), MASK[mask], int(window or 0), scale
 
 
+@functools.lru_cache(maxsize=4096)
+def _fwd_scratch_bytes(*sizes):
+    """af_fwd_workspace_bytes, a pure function of the sizes (a dictionary lookup costs the smallest calls less)."""
+    return _lib.load().af_fwd_workspace_bytes(*sizes)
+
+
+def _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, blocks=0):
+    """Scratch for keys rotated once ahead of a forward, where that is faster
+    (af_fwd_workspace_bytes), else None.  Without memory for it the keys are
+    rotated in the loop: the same result."""
+    n = _fwd_scratch_bytes(B, H, Hkv, S, D, DTYPE[q.dtype], r, m, w, blocks) if r else 0
+    if n == 0:
+        return None
+    try:
+        return torch.empty(n, device=q.device, dtype=torch.uint8)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def attnfuse_fwd(q, k, v, *, rope="none", theta=10000.0, mask="causal", window=None,
                  alibi_slopes=None, scale=None, out=None, lse=None, rope_table=None):
     """O, LSE = attention(q, k, v); see attnfuse_fwd in include/attnfuse.h."""
@@ -186,7 +206,14 @@ def attnfuse_fwd(q, k, v, *, rope="none", theta=10000.0, mask="causal", window=N
     r, th, m, w, sc = _variant(rope, theta, mask, window, alibi_slopes, scale, D, H, dev)
     tab = _table(rope, theta, D, S, dev, rope_table)
     tp, tr = _tab(tab)
+    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w)
     with torch.cuda.device(dev):
+        if ws is not None:
+            code = _lib.load().af_fwd_ws(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), None, None, None, 0, 0, 0, 0,
+                                         ws.data_ptr(), ws.numel(), B, H, Hkv, S, D, DTYPE[q.dtype], r, th, tp, tr, m,
+                                         w, _ptr(alibi_slopes), sc, _stream())
+            _check(code, "attnfuse_fwd")
+            return out, lse
         code = _lib.load().attnfuse_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), B, H, Hkv, S, D,
                                         DTYPE[q.dtype], r, th, tp, tr, m, w, _ptr(alibi_slopes), sc, _stream())
     _check(code, "attnfuse_fwd")
@@ -246,7 +273,14 @@ def attnfuse_fwd_blocksparse(q, k, v, block_mask, *, rope="none", theta=10000.0,
     r, th, m, w, sc = _variant(rope, theta, mask, window, alibi_slopes, scale, D, H, dev)
     tab = _table(rope, theta, D, S, dev, rope_table)
     tp, tr = _tab(tab)
+    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, max(1, block_mask.k_idx.numel()))
     with torch.cuda.device(dev):
+        if ws is not None:
+            code = _lib.load().af_fwd_ws(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), qp, ki, None, 0, 0, 0, 0,
+                                         ws.data_ptr(), ws.numel(), B, H, Hkv, S, D, DTYPE[q.dtype], r, th, tp, tr, m,
+                                         w, _ptr(alibi_slopes), sc, _stream())
+            _check(code, "attnfuse_fwd_blocksparse")
+            return out, lse
         code = _lib.load().attnfuse_fwd_blocksparse(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), qp, ki,
                                                     B, H, Hkv, S, D, DTYPE[q.dtype], r, th, tp, tr, m, w,
                                                     _ptr(alibi_slopes), sc, _stream())
@@ -308,7 +342,14 @@ def attnfuse_fwd_bias_norm(q, k, v, *, bias=None, norm="softmax", rope="none", t
     r, th, m, w, sc = _variant(rope, theta, mask, window, None, scale, D)
     tab = _table(rope, theta, D, S, dev, rope_table)
     tp, tr = _tab(tab)
+    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w)
     with torch.cuda.device(dev):
+        if ws is not None:
+            code = _lib.load().af_fwd_ws(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), None, None, bp, sb, sh, sq,
+                                         NORM[norm], ws.data_ptr(), ws.numel(), B, H, Hkv, S, D, DTYPE[q.dtype], r,
+                                         th, tp, tr, m, w, None, sc, _stream())
+            _check(code, "attnfuse_fwd_bias_norm")
+            return out, lse
         code = _lib.load().attnfuse_fwd_bias_norm(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), bp, sb, sh,
                                                   sq, NORM[norm], B, H, Hkv, S, D, DTYPE[q.dtype], r, th, tp, tr, m, w,
                                                   None, sc, _stream())

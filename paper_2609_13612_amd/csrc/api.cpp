@@ -11,6 +11,7 @@
 #include <cstdint>
 #include <cstring>
 
+#include "binding.h"
 #include "launch.hpp"
 
 namespace {
@@ -152,7 +153,7 @@ int check_ext(const Ext& e, const void* const* outs, int nouts) {
 int fwd_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, const int* q_block_ptr,
              const int* k_block_idx, const Ext& ext, int B, int H, int H_kv, int S, int D, int dtype, int rope,
              float rope_theta, const float* rope_table, int rope_table_rows, int mask, int window,
-             const float* alibi_slopes, float softmax_scale, void* stream) {
+             const float* alibi_slopes, float softmax_scale, void* stream, void* k16 = nullptr, size_t k16_bytes = 0) {
   const bool relu = ext.norm == AF_NORM_RELU;   // no row statistic: LSE may be NULL
   if (!Q || !K || !V || !O || (!LSE && !relu)) return AF_ERR_INVALID_ARG;
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(O) || !aligned16(LSE)) return AF_ERR_INVALID_ARG;
@@ -185,6 +186,14 @@ int fwd_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, c
   p.bias = ext.bias;
   p.bias_sb = ext.sb; p.bias_sh = ext.sh; p.bias_sq = ext.sq;
   const bool alibi = alibi_slopes != nullptr;
+  if (k16) {   // keys rotated once into the workspace
+    const void* kin[] = {Q, K, V, O, LSE, ext.bias, q_block_ptr, k_block_idx, rope_table};
+    for (const void* x : kin) if (x == k16) return AF_ERR_INVALID_ARG;
+    if (!aligned16(k16) || dtype != AF_DTYPE_BF16 || rope == AF_ROPE_NONE) return AF_ERR_INVALID_ARG;
+    if (k16_bytes < (size_t)B * H_kv * S * D * 2) return AF_ERR_INVALID_ARG;
+    p.k16 = k16;
+    return map_launch(af::launch_fwd_prerot(D, rope, mask, alibi, ext.kind(), p, st));
+  }
   if (dtype == AF_DTYPE_BF16) return map_launch(af::launch_fwd_bf16(D, rope, mask, alibi, ext.kind(), p, st));
   return map_launch(af::launch_fwd_fp32(D, rope, mask, alibi, p, st));
 }
@@ -311,6 +320,66 @@ int attnfuse_fwd_bias_norm(const void* Q, const void* K, const void* V, void* O,
   e.bias = bias; e.sb = bias_stride_b; e.sh = bias_stride_h; e.sq = bias_stride_q; e.norm = norm;
   return fwd_impl(Q, K, V, O, LSE, nullptr, nullptr, e, B, H, H_kv, S, D, dtype, rope, rope_theta, rope_table,
                   rope_table_rows, mask, window, alibi_slopes, softmax_scale, stream);
+}
+
+// Rotating the keys once costs a launch and a pass over K (read bf16, write
+// fp16); rotating them in the loop costs every workgroup VALU work on every
+// tile it visits.  Measured on MI355X (the two forms in turn, eager calls):
+//   B1 H32/8 D128 causal S 512 / 1024 / 2048 / 4096 / 8192: in-loop 25.2 / 39.4 / 69.1 / 167 / 621 us, rotated once
+//   25.6 / 38.0 / 65.2 / 154 / 558 us; B4 H12 D64 no mask S 1024 / 2048 / 4096: 26.3 / 91.3 / 276 and 29.8 / 91.6 /
+//   261 us; B4 H32/8 S8192 window 1024: 763 and 688 us; block-sparse B4 H12 S4096 D64 (9.2 % active): 123 and 82 us.
+// These fit a launch of 2.6 us plus the pass at 4.5 TB/s against 0.27 us
+// (D = 128), 0.135 us (D = 64) or 0.6 us (block-sparse) for each tile that the
+// busiest CU rotates.  D = 64 loses below that line, so both forms stay.
+size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, int rope, int mask, int window,
+                              long long sparse_blocks) {
+  if (B < 1 || H < 1 || H_kv < 1 || S < 1 || S > kMaxS || H % H_kv || !supported_d(D) || dtype != AF_DTYPE_BF16 ||
+      rope == AF_ROPE_NONE)
+    return 0;
+  const size_t bytes = (size_t)B * H_kv * S * D * 2;
+  const int G = H / H_kv;
+  int hp = 1;                       // query heads per workgroup, as the launcher packs them
+  while (hp < (sparse_blocks ? 4 : 8) && G % (2 * hp) == 0) hp *= 2;
+  const double units = (double)B * H_kv * (G / hp);
+  const double nt = (S + 63) / 64;
+  double tiles, longest;            // key tiles visited per unit, and by the longest workgroup
+  if (sparse_blocks) {
+    tiles = (double)sparse_blocks * (mask == AF_MASK_NONE ? 1.0 : 0.5);
+    longest = 0;                    // shared by key groups
+  } else {
+    const double rows = 256.0 / hp, wgs = std::ceil(S / rows);
+    longest = nt;
+    tiles = wgs * nt;
+    if (mask == AF_MASK_CAUSAL) tiles = wgs * (nt + rows / 64.0) / 2.0;
+    if (mask == AF_MASK_SLIDING_WINDOW) {
+      longest = std::fmin(nt, (rows + window) / 64.0 + 1.0);
+      tiles = std::fmin(wgs * (nt + rows / 64.0) / 2.0, wgs * longest);
+    }
+  }
+  const double per_tile = sparse_blocks ? 0.6 : (D == 128 ? 0.27 : 0.135);
+  const double saved = per_tile * std::fmax(longest, units * tiles / 256.0);
+  return saved > 2.6 + (double)bytes * 2.0 / 4.5e6 ? bytes : 0;
+}
+
+int af_fwd_ws(const void* Q, const void* K, const void* V, void* O, float* LSE, const int* q_block_ptr,
+              const int* k_block_idx, const float* bias, long long bias_stride_b, long long bias_stride_h,
+              long long bias_stride_q, int norm, void* workspace, size_t workspace_bytes,
+              int B, int H, int H_kv, int S, int D, int dtype,
+              int rope, float rope_theta, const float* rope_table, int rope_table_rows, int mask, int window,
+              const float* alibi_slopes, float softmax_scale, void* stream) {
+  if (!workspace) return AF_ERR_INVALID_ARG;
+  if ((q_block_ptr == nullptr) != (k_block_idx == nullptr) || !aligned4(q_block_ptr) || !aligned4(k_block_idx))
+    return AF_ERR_INVALID_ARG;
+  if (q_block_ptr) {
+    const void* outs[] = {O, LSE};
+    for (const void* x : outs)
+      if (x == (const void*)q_block_ptr || x == (const void*)k_block_idx) return AF_ERR_INVALID_ARG;
+    if (S < 1 || S > kMaxSparseS) return AF_ERR_INVALID_ARG;
+  }
+  Ext e;
+  e.bias = bias; e.sb = bias_stride_b; e.sh = bias_stride_h; e.sq = bias_stride_q; e.norm = norm;
+  return fwd_impl(Q, K, V, O, LSE, q_block_ptr, k_block_idx, e, B, H, H_kv, S, D, dtype, rope, rope_theta, rope_table,
+                  rope_table_rows, mask, window, alibi_slopes, softmax_scale, stream, workspace, workspace_bytes);
 }
 
 size_t attnfuse_bwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int rope) {

@@ -1,0 +1,35 @@
+/*
+ * Entry points of the library that only the Python binding calls: forms of
+ * the public calls (include/attnfuse.h) that take scratch memory.  They are not
+ * part of the C ABI and may change with the binding.
+ */
+#ifndef AF_BINDING_H
+#define AF_BINDING_H
+
+#include <stddef.h>
+
+#ifdef __cplusplus
+extern "C" {
+#endif
+
+/* Bytes of scratch with which the forward of these sizes runs faster (the keys
+ * rotated once into it), or 0 where it is better without.  sparse_blocks: the
+ * active blocks of a block mask, 0 without one. */
+size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, int rope, int mask, int window,
+                              long long sparse_blocks);
+
+/* attnfuse_fwd (bias == NULL, q_block_ptr == NULL), attnfuse_fwd_bias_norm or
+ * attnfuse_fwd_blocksparse with RoPE on bf16 tensors, given
+ * 2 * B * H_kv * S * D bytes of 16-byte aligned device scratch; same results. */
+int af_fwd_ws(const void* Q, const void* K, const void* V, void* O, float* LSE, const int* q_block_ptr,
+              const int* k_block_idx, const float* bias, long long bias_stride_b, long long bias_stride_h,
+              long long bias_stride_q, int norm, void* workspace, size_t workspace_bytes,
+              int B, int H, int H_kv, int S, int D, int dtype,
+              int rope, float rope_theta, const float* rope_table, int rope_table_rows, int mask, int window,
+              const float* alibi_slopes, float softmax_scale, void* stream);
+
+#ifdef __cplusplus
+}
+#endif
+
+#endif

@@ -22,6 +22,7 @@ struct FwdParams {
   float scale;
   const float2* table;    // [rows >= S][D/2] (cos, sin); nullptr without RoPE
   int heads_per_wg;       // set by the bf16 launcher: query heads packed per workgroup
+  void* k16;              // workspace [B, H_kv, S, D] fp16: K' = R K, or nullptr (keys rotated in the loop)
   const int* bq_ptr;      // block-sparse mask by 64-row query block (CSR row pointers), or nullptr
   const int* bk_idx;      // and the active 64-key blocks of each row
   const float* bias;      // dense bias: element (b, h, i, j) at bias[b*bias_sb + h*bias_sh + i*bias_sq + j]
@@ -87,6 +88,8 @@ struct RopeParams {
 // Return 0 on success, -2 when the variant is not compiled, -3 on a HIP error.
 // ext: EXT_* (common.hpp); variants other than EXT_NONE run without ALiBi and block masks.
 int launch_fwd_bf16(int D, int rope, int mask, bool alibi, int ext, const FwdParams& p, hipStream_t st);
+// The same with p.k16 filled first (RoPE kinds only): two launches.
+int launch_fwd_prerot(int D, int rope, int mask, bool alibi, int ext, const FwdParams& p, hipStream_t st);
 int launch_fwd_fp32(int D, int rope, int mask, bool alibi, const FwdParams& p, hipStream_t st);
 int launch_bwd_bf16(int D, int rope, int mask, bool alibi, int ext, const BwdParams& p, hipStream_t st);
 // The dK/dV pass alone (the last launch of launch_bwd_bf16).
@@ -94,6 +97,8 @@ int launch_bwd_dkdv_bf16(int D, int rope, int mask, bool alibi, int ext, const B
 int launch_bwd_fp32(int D, int rope, int mask, bool alibi, const BwdParams& p, hipStream_t st);
 int launch_decode(int D, int rope, bool alibi, const DecodeParams& p, hipStream_t st);
 int launch_rope(bool fp32, int D, int rope, bool inverse, const RopeParams& p, hipStream_t st);
+// x0 (bf16) rotated into y0 (fp16); x1 unused.
+int launch_rope_f16(int D, int rope, const RopeParams& p, hipStream_t st);
 int launch_rope_table(float2* table, int rows, int D, double theta, hipStream_t st);
 
 // Static device scratch of the decode entry point that allocates nothing: its

@@ -50,17 +50,15 @@ __device__ __forceinline__ void rotate_interleaved4_f32(float4& x, const float2*
 }
 
 // ---------------------------------------------------------------- rotation
-constexpr int ROPE_HEADS_PER_THREAD = 8;
-
 // Thread item: (head group, batch, position n, chunk c).  For NeoX an item is
 // the chunk pair (c, c + D/2); for interleaved a single chunk.  A thread loads
 // its cos/sin entries once, issues the loads of all its heads before rotating
-// any of them (memory-level parallelism), then stores.
-template <bool FP32, int D, int ROPE, bool INV>
+// any of them (memory-level parallelism), then stores.  F16OUT: bf16 in,
+// fp16 out (the rotated keys the attention kernels read).
+template <bool FP32, int D, int ROPE, bool INV, int HPT, bool F16OUT = false>
 __global__ __launch_bounds__(256) void rope_kernel(RopeParams p) {
   constexpr int E = FP32 ? 4 : 8;                                  // elements per 16-byte chunk
   constexpr int CPR = (ROPE == ROPE_NEOX) ? D / (2 * E) : D / E;   // items per row
-  constexpr int HPT = ROPE_HEADS_PER_THREAD;
   constexpr int NCH = (ROPE == ROPE_NEOX) ? 2 : 1;                 // chunks per item
   constexpr int NT = (ROPE == ROPE_NEOX) ? E / 2 : E / 4;          // float4 of cos/sin per item
   constexpr int EB = FP32 ? 4 : 2;                                 // bytes per element
@@ -104,8 +102,8 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeParams p) {
       }
       x[j][0] = __builtin_bit_cast(u32x4, a);
     } else {
-      if constexpr (ROPE == ROPE_NEOX) rotate_neox8<INV>(x[j][0], x[j][1], t);
-      else rotate_interleaved8<INV>(x[j][0], t);
+      if constexpr (ROPE == ROPE_NEOX) rotate_neox8<INV, F16OUT>(x[j][0], x[j][1], t);
+      else rotate_interleaved8<INV, F16OUT>(x[j][0], t);
     }
   }
 #pragma unroll
@@ -122,15 +120,15 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeParams p) {
   }
 }
 
-template <bool FP32, int D, int ROPE, bool INV>
+template <bool FP32, int D, int ROPE, bool INV, int HPT = 8, bool F16OUT = false>
 static int launch_rope_one(const RopeParams& p, hipStream_t st) {
   constexpr int E = FP32 ? 4 : 8;
   constexpr int CPR = (ROPE == ROPE_NEOX) ? D / (2 * E) : D / E;
   const int nh = p.heads0 + p.heads1;
-  const long long ngroups = (nh + ROPE_HEADS_PER_THREAD - 1) / ROPE_HEADS_PER_THREAD;
+  const long long ngroups = (nh + HPT - 1) / HPT;
   const long long total = (long long)p.S * CPR * p.B * ngroups;
   const unsigned blocks = (unsigned)((total + 255) / 256);
-  hipLaunchKernelGGL((rope_kernel<FP32, D, ROPE, INV>), dim3(blocks), dim3(256), 0, st, p);
+  hipLaunchKernelGGL((rope_kernel<FP32, D, ROPE, INV, HPT, F16OUT>), dim3(blocks), dim3(256), 0, st, p);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
@@ -152,6 +150,17 @@ int launch_rope(bool fp32, int D, int rope, bool inverse, const RopeParams& p, h
     if (D == 64) return rope_dispatch<false, 64>(rope, inverse, p, st);
     if (D == 128) return rope_dispatch<false, 128>(rope, inverse, p, st);
   }
+  return -2;
+}
+
+// bf16 x0 -> fp16 y0 (the rotated keys of the attention kernels).
+int launch_rope_f16(int D, int rope, const RopeParams& p, hipStream_t st) {
+  if (rope == ROPE_NEOX)
+    return D == 64 ? launch_rope_one<false, 64, ROPE_NEOX, false, 4, true>(p, st)
+                   : launch_rope_one<false, 128, ROPE_NEOX, false, 4, true>(p, st);
+  if (rope == ROPE_INTERLEAVED)
+    return D == 64 ? launch_rope_one<false, 64, ROPE_INTERLEAVED, false, 4, true>(p, st)
+                   : launch_rope_one<false, 128, ROPE_INTERLEAVED, false, 4, true>(p, st);
   return -2;
 }
 

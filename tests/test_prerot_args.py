@@ -1,0 +1,39 @@
+"""The binding's forward on keys rotated once: which calls it takes, and its
+argument checks (CPU; validation fails before any HIP call)."""
+import pytest
+
+from paper_2609_13612_amd import _lib
+
+FAKE = 0x10000
+
+
+def _bytes(B=1, H=32, Hkv=8, S=8192, D=128, dtype=0, rope=1, mask=1, window=0, blocks=0):
+    return _lib.load().af_fwd_workspace_bytes(B, H, Hkv, S, D, dtype, rope, mask, window, blocks)
+
+
+def test_long_rotated_prompts_take_the_scratch():
+    for rope in (1, 2):
+        assert _bytes(rope=rope) == 2 * 8 * 8192 * 128
+    assert _bytes(B=4, mask=2, window=1024) == 2 * 4 * 8 * 8192 * 128
+    assert _bytes(B=4, H=12, Hkv=12, S=4096, D=64, mask=0, blocks=377) == 2 * 4 * 12 * 4096 * 64
+
+
+@pytest.mark.parametrize("kw", [
+    dict(rope=0), dict(dtype=1), dict(S=256), dict(S=0), dict(B=0), dict(H=6, Hkv=4), dict(D=96), dict(S=(1 << 20) + 1),
+    dict(H=12, Hkv=12, B=4, S=512, D=64), dict(mask=2, window=1)])
+def test_other_calls_do_not(kw):
+    assert _bytes(**kw) == 0
+
+
+BASE = dict(Q=FAKE, K=FAKE + 0x100, V=FAKE + 0x200, O=FAKE + 0x300, LSE=FAKE + 0x400, qp=None, ki=None, bias=None, sb=0,
+            sh=0, sq=0, norm=0, ws=FAKE + 0x500, n=1 << 20, B=1, H=4, Hkv=2, S=16, D=64, dtype=0, rope=1, theta=1e4,
+            table=0x40000, rows=4096, mask=1, window=0, slopes=None, scale=0.125, stream=None)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(ws=None), dict(ws=FAKE + 0x508), dict(ws=FAKE), dict(ws=FAKE + 0x300), dict(ws=0x40000), dict(n=2 * 2 * 16 * 64 - 1),
+    dict(rope=0), dict(dtype=1), dict(Q=None), dict(S=0), dict(qp=FAKE + 0x600), dict(ki=FAKE + 0x600),
+    dict(qp=FAKE + 0x602, ki=FAKE + 0x700), dict(qp=FAKE + 0x300, ki=FAKE + 0x700),
+    dict(qp=FAKE + 0x600, ki=FAKE + 0x700, S=64 * 2048 + 1), dict(rows=8), dict(scale=0.0), dict(norm=2)])
+def test_bad_arguments_are_refused(kw):
+    assert _lib.load().af_fwd_ws(*{**BASE, **kw}.values()) == -1
