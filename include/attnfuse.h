@@ -50,7 +50,7 @@ extern "C" {
 #endif
 
 /* Element type of Q, K, V, O, dO, dQ, dK, dV.  fp32 is the debug path: same
- * method, fp32 arithmetic throughout, no MFMA, one row per thread. */
+ * method, fp32 arithmetic throughout (fp32 matrix instructions). */
 enum { AF_DTYPE_BF16 = 0, AF_DTYPE_FP32 = 1 };
 
 /* RoPE pairing (Section 4.1 "Fused RoPE": the paper's NeoX convention pairs

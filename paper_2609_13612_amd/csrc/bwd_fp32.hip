@@ -1,240 +1,236 @@
-// fp32 debug backward: the same three passes as the bf16 backward (Section
-// 4.4: row statistics; dK/dV over query tiles with the GQA group's heads
-// summed; dQ over key tiles; no atomics), in plain fp32 FMA arithmetic with one
-// row per thread and the rotation recomputed on every staged tile.  It exists
-// to check the backward at fp32 precision, not for speed.
+// fp32 debug backward: the passes of the bf16 backward (Section 4.4: dQ over
+// key tiles; dK/dV over query tiles with the GQA group's heads summed; no
+// atomics) in fp32 arithmetic throughout, the rotation recomputed on every
+// tile.  It exists to check the backward at fp32 precision.
 //
 // With s_ij = scale <R_i q_i, R_j k_j> + bias_ij and P the softmax rows:
 //   dV_j  = sum_i P_ij dO_i
 //   dP_ij = <dO_i, v_j>,  delta_i = sum_d dO_id O_id,  dS_ij = P_ij (dP_ij - delta_i)
 //   dQ_i  = R_i^T (scale sum_j dS_ij R_j k_j),  dK_j = R_j^T (scale sum_i dS_ij R_i q_i)
 // P_ij is re-derived from the forward's LSE: P_ij = exp(s_ij - LSE_i).
-#include "common.hpp"
+//
+// One workgroup per 16 output rows, its waves on the other side's 16-row tiles
+// in turn (fp32_tiles.hpp).  The dQ pass forms delta for its own rows from
+// registers and leaves it in the workspace for the dK/dV pass, so there is no
+// pass of its own for it.  Bound, as the forward, by the chain of tiles of the
+// longest wave.  Against one row per thread of 64: B1 H2 S128 D64 (interleaved,
+// causal) dQ 139 -> 9.5 us, dK/dV 245 -> 9.2 us, and the row statistics' own
+// pass (17 us) is gone; B1 H32/8 S2048 D128 (NeoX, causal) 210 -> 2.2 ms.
+#include "fp32_tiles.hpp"
 #include "launch.hpp"
 
 namespace af {
 
-constexpr int B32_ROWS = 64;   // rows per workgroup (one wave)
-constexpr int B32_BT = 32;     // rows per staged tile
+// LDS: each wave's transposition tile, then the merge of the waves' partials.
+template <int D>
+constexpr int B32_LDS = F32_XCH<D> > F32_NW * F32_T * (D + 4) ? F32_XCH<D> : F32_NW * F32_T * (D + 4);
 
-// delta_i and LSE_i in log2 units (+inf for an empty row, so its P is 0).
-__global__ void bwd_fp32_prep_kernel(BwdParams p, int D) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long long)p.B * p.H * p.S) return;
-  const float* __restrict__ dO = static_cast<const float*>(p.dout) + i * D;
-  const float* __restrict__ O = static_cast<const float*>(p.o) + i * D;
-  float s = 0.f;
-  for (int d = 0; d < D; ++d) s = __builtin_fmaf(dO[d], O[d], s);
-  p.delta[i] = s;
-  const float l = p.lse[i];
-  p.lse2[i] = (l == -INFINITY) ? INFINITY : l * kLog2e;
-}
-
-// One query row per thread: loops over the visible key tiles, each staged in
-// LDS with K rotated by the first B32_BT threads.
 template <int D, int ROPE, int MASK, bool ALIBI>
-__global__ __launch_bounds__(64) void bwd_fp32_dq_kernel(BwdParams p) {
-  __shared__ float Kf[B32_BT][D + 1];
-  __shared__ float Vf[B32_BT][D + 1];
-  const int tid = threadIdx.x;
+__global__ __launch_bounds__(64 * F32_NW) void bwd_fp32_dq_kernel(BwdParams p) {
+  constexpr int DL = D / 4, MT = D / 16;
+  __shared__ __attribute__((aligned(16))) float lds[B32_LDS<D>];
+  const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = p.S;
   const int BH = p.B * p.H;
+  const int nqb = (S + F32_T - 1) / F32_T;
   const int bh = blockIdx.x % BH;
-  const int qb = (int)(blockIdx.x / BH);
+  const int qb = nqb - 1 - (int)(blockIdx.x / BH);   // the longest causal rows first
   const int b = bh / p.H, h = bh % p.H;
-  const int g = h / (p.H / p.Hkv);
-  const int m0 = qb * B32_ROWS;
-  const int m = m0 + tid;
-  const bool live = m < S;
-  const float* __restrict__ Q = static_cast<const float*>(p.q) + (size_t)bh * S * D;
-  const float* __restrict__ dO = static_cast<const float*>(p.dout) + (size_t)bh * S * D;
-  const float* __restrict__ K = static_cast<const float*>(p.k) + (size_t)(b * p.Hkv + g) * S * D;
-  const float* __restrict__ V = static_cast<const float*>(p.v) + (size_t)(b * p.Hkv + g) * S * D;
-
-  float q[D], dov[D], dq[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    q[d] = live ? Q[(size_t)m * D + d] : 0.f;
-    dov[d] = live ? dO[(size_t)m * D + d] : 0.f;
-    dq[d] = 0.f;
-  }
-  if (ROPE != ROPE_NONE && live) rotate_row_f32<D, ROPE>(q, p.table + (size_t)m * (D / 2));
-  const float l2 = live ? p.lse2[(size_t)bh * S + m] : INFINITY;
-  const float dl = live ? p.delta[(size_t)bh * S + m] : 0.f;
+  const size_t kv = (size_t)(b * p.Hkv + h / (p.H / p.Hkv)) * S * D;
+  const int m0 = qb * F32_T, m = m0 + lq, mc = min(m, S - 1);
+  const size_t row = ((size_t)bh * S + mc) * D;
+  const float* __restrict__ K = static_cast<const float*>(p.k) + kv;
+  const float* __restrict__ V = static_cast<const float*>(p.v) + kv;
 
   const float c2 = p.scale * kLog2e;
   const float slope2 = ALIBI ? p.slopes[h] * kLog2e : 0.f;
   const int W = p.window;
-  const int ntiles = (S + B32_BT - 1) / B32_BT;
-  int t_begin = 0, t_end = ntiles;
-  if constexpr (MASK != MASK_NONE) t_end = min(ntiles, (min(m0 + B32_ROWS, S) - 1) / B32_BT + 1);
-  if constexpr (MASK == MASK_SLIDING_WINDOW) t_begin = max(0, m0 - W + 1) / B32_BT;
+  int t = wave, t_end = nqb;
+  if constexpr (MASK != MASK_NONE) t_end = qb + 1;
+  if constexpr (MASK == MASK_SLIDING_WINDOW) t += max(0, m0 - W + 1) / F32_T;
 
-  for (int t = t_begin; t < t_end; ++t) {
-    const int n0 = t * B32_BT;
-    __syncthreads();
-    for (int r = 0; r < B32_BT; ++r) {
+  float k[DL], cs[DL], vv[DL];   // the tile in flight; rows past S: row S-1, masked
+  auto load = [&](int tile) {
+    const int n = min(tile * F32_T + lq, S - 1);
+    f32_load_row<D>(k, K + (size_t)n * D, g);
+    f32_load_cs<D, ROPE>(cs, p.table + (size_t)n * (D / 2), g);
+    f32_load_row<D>(vv, V + (size_t)n * D, g);
+  };
+  if (t < t_end) load(t);
+  float q[DL], dov[DL];
+  f32_load_row<D>(q, static_cast<const float*>(p.q) + row, g);
+  f32_load_row<D>(dov, static_cast<const float*>(p.dout) + row, g);
+  float dl = 0.f;
+  {
+    float x[DL];
+    f32_load_cs<D, ROPE>(x, p.table + (size_t)mc * (D / 2), g);
+    f32_rotate<D, ROPE>(q, x);
+    f32_load_row<D>(x, static_cast<const float*>(p.o) + row, g);
+#pragma unroll
+    for (int i = 0; i < DL; ++i) dl = __builtin_fmaf(dov[i], x[i], dl);
+    dl = groups_sum(dl);
+  }
+  const float l = p.lse[(size_t)bh * S + mc];
+  const float l2 = (l == -INFINITY) ? INFINITY : l * kLog2e;
+  if (wave == 0 && g == 0 && m < S) p.delta[(size_t)bh * S + m] = dl;
+
+  f32x4 dq[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) dq[i] = f32x4{};
+  for (; t < t_end; t += F32_NW) {
+    const int n0 = t * F32_T + 4 * g;     // key of element 0
+    float kr[DL], v[DL], kt[DL];
+#pragma unroll
+    for (int i = 0; i < DL; ++i) {
+      kr[i] = k[i];
+      v[i] = vv[i];
+    }
+    f32_rotate<D, ROPE>(kr, cs);
+    if (t + F32_NW < t_end) load(t + F32_NW);
+    f32_transpose<D>(kt, kr, lds + wave * F32_T * (D + 4), lq, g);
+    const f32x4 s = f32_dot<D>(kr, q), dp = f32_dot<D>(v, dov);
+    float ds[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
       const int n = n0 + r;
-      for (int d = tid; d < D; d += B32_ROWS) {
-        Kf[r][d] = (n < S) ? K[(size_t)n * D + d] : 0.f;
-        Vf[r][d] = (n < S) ? V[(size_t)n * D + d] : 0.f;
-      }
-    }
-    __syncthreads();
-    if (ROPE != ROPE_NONE && tid < B32_BT && n0 + tid < S) {
-      float row[D];
-#pragma unroll
-      for (int d = 0; d < D; ++d) row[d] = Kf[tid][d];
-      rotate_row_f32<D, ROPE>(row, p.table + (size_t)(n0 + tid) * (D / 2));
-#pragma unroll
-      for (int d = 0; d < D; ++d) Kf[tid][d] = row[d];
-    }
-    __syncthreads();
-    if (!live) continue;
-    for (int j = 0; j < B32_BT; ++j) {
-      const int n = n0 + j;
       bool ok = n < S;
       if constexpr (MASK != MASK_NONE) ok = ok && (n <= m);
       if constexpr (MASK == MASK_SLIDING_WINDOW) ok = ok && (n > m - W);
-      if (!ok) continue;
-      float s = 0.f, dp = 0.f;
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        s = __builtin_fmaf(q[d], Kf[j][d], s);
-        dp = __builtin_fmaf(dov[d], Vf[j][d], dp);
-      }
-      const float x = ALIBI ? __builtin_fmaf(s, c2, slope2 * (float)(n - m)) : s * c2;
-      const float pr = exp2f(x - l2);
-      const float ds = pr * (dp - dl);
-#pragma unroll
-      for (int d = 0; d < D; ++d) dq[d] = __builtin_fmaf(ds, Kf[j][d], dq[d]);
+      const float x = ALIBI ? __builtin_fmaf(s[r], c2, slope2 * (float)(n - m)) : s[r] * c2;
+      ds[r] = ok ? exp2f(x - l2) * (dp[r] - dl) : 0.f;
     }
+    f32_accumulate<D>(dq, kt, ds);
   }
-  if (!live) return;
-#pragma unroll
-  for (int d = 0; d < D; ++d) dq[d] *= p.scale;
-  if (ROPE != ROPE_NONE) rotate_row_f32<D, ROPE, true>(dq, p.table + (size_t)m * (D / 2));
-  float* dQ = static_cast<float*>(p.dq) + ((size_t)bh * S + m) * D;
-#pragma unroll
-  for (int d = 0; d < D; ++d) dQ[d] = dq[d];
+
+  __syncthreads();   // every wave is past its transposition tile
+  f32_put<D>(lds, dq, wave, lane);
+  __syncthreads();
+  if (wave < D / 32 && m < S) {
+    const float w[F32_NW] = {p.scale, p.scale, p.scale, p.scale};
+    f32x4 out[2];
+    f32_get<D>(out, lds, w, wave, lane);
+    f32_rotate_back<D, ROPE>(out, p.table + (size_t)m * (D / 2), wave, g);
+    f32_store<D>(static_cast<float*>(p.dq) + ((size_t)bh * S + m) * D, out, wave, g);
+  }
 }
 
-// One key row per thread (of one batch and K/V head): loops over the group's
-// query heads and their visible query tiles, each staged in LDS with Q rotated
-// by the first B32_BT threads, dO, and the rows' statistics.
+// 16 keys of one (batch, K/V head); the waves take the (query head of the
+// group, query tile) pairs in turn.
 template <int D, int ROPE, int MASK, bool ALIBI>
-__global__ __launch_bounds__(64) void bwd_fp32_dkdv_kernel(BwdParams p) {
-  __shared__ float Qf[B32_BT][D + 1];
-  __shared__ float Of[B32_BT][D + 1];
-  __shared__ float Lf[B32_BT], Df[B32_BT];
-  const int tid = threadIdx.x;
+__global__ __launch_bounds__(64 * F32_NW) void bwd_fp32_dkdv_kernel(BwdParams p) {
+  constexpr int DL = D / 4, MT = D / 16;
+  __shared__ __attribute__((aligned(16))) float lds[B32_LDS<D>];
+  const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = p.S;
   const int BG = p.B * p.Hkv;
   const int bg = blockIdx.x % BG;
-  const int kb = (int)(blockIdx.x / BG);
-  const int b = bg / p.Hkv, g = bg % p.Hkv;
+  const int kb = (int)(blockIdx.x / BG);   // ascending: under a causal mask the first keys see the most queries
+  const int b = bg / p.Hkv;
   const int G = p.H / p.Hkv;
-  const int n0 = kb * B32_ROWS;
-  const int n = n0 + tid;
-  const bool live = n < S;
-  const float* __restrict__ K = static_cast<const float*>(p.k) + (size_t)bg * S * D;
-  const float* __restrict__ V = static_cast<const float*>(p.v) + (size_t)bg * S * D;
-
-  float k[D], vv[D], dk[D], dv[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    k[d] = live ? K[(size_t)n * D + d] : 0.f;
-    vv[d] = live ? V[(size_t)n * D + d] : 0.f;
-    dk[d] = 0.f;
-    dv[d] = 0.f;
-  }
-  if (ROPE != ROPE_NONE && live) rotate_row_f32<D, ROPE>(k, p.table + (size_t)n * (D / 2));
+  const int h0 = (bg % p.Hkv) * G;
+  const int n0 = kb * F32_T, n = n0 + lq, nc = min(n, S - 1);
 
   const float c2 = p.scale * kLog2e;
   const int W = p.window;
-  const int ntiles = (S + B32_BT - 1) / B32_BT;
-  const int n_last = min(n0 + B32_ROWS, S) - 1;
-  int t_begin = 0, t_end = ntiles;
-  if constexpr (MASK != MASK_NONE) t_begin = n0 / B32_BT;
-  if constexpr (MASK == MASK_SLIDING_WINDOW) t_end = min(ntiles, (n_last + W - 1) / B32_BT + 1);
+  int tq = 0, tq_end = (S + F32_T - 1) / F32_T;
+  if constexpr (MASK != MASK_NONE) tq = kb;
+  if constexpr (MASK == MASK_SLIDING_WINDOW) tq_end = min(tq_end, (min(n0 + F32_T, S) - 1 + W - 1) / F32_T + 1);
+  const int nt = tq_end - tq, items = G * nt;
 
-  for (int hh = 0; hh < G; ++hh) {
-    const int h = g * G + hh;
-    const size_t bh = (size_t)b * p.H + h;
-    const float* __restrict__ Q = static_cast<const float*>(p.q) + bh * S * D;
-    const float* __restrict__ dO = static_cast<const float*>(p.dout) + bh * S * D;
-    const float slope2 = ALIBI ? p.slopes[h] * kLog2e : 0.f;
-    for (int t = t_begin; t < t_end; ++t) {
-      const int m0 = t * B32_BT;
-      __syncthreads();
-      for (int r = 0; r < B32_BT; ++r) {
-        const int m = m0 + r;
-        for (int d = tid; d < D; d += B32_ROWS) {
-          Qf[r][d] = (m < S) ? Q[(size_t)m * D + d] : 0.f;
-          Of[r][d] = (m < S) ? dO[(size_t)m * D + d] : 0.f;
-        }
-      }
-      if (tid < B32_BT) {
-        const int m = m0 + tid;
-        Lf[tid] = (m < S) ? p.lse2[bh * S + m] : INFINITY;
-        Df[tid] = (m < S) ? p.delta[bh * S + m] : 0.f;
-      }
-      __syncthreads();
-      if (ROPE != ROPE_NONE && tid < B32_BT && m0 + tid < S) {
-        float row[D];
+  float q[DL], cs[DL], dor[DL], dot[DL], l4[4], d4[4];   // the tile in flight
+  auto load = [&](int it) {
+    const size_t bh = (size_t)b * p.H + h0 + it / nt;
+    const int m0 = (tq + it % nt) * F32_T, m = min(m0 + lq, S - 1);
+    f32_load_row<D>(q, static_cast<const float*>(p.q) + (bh * S + m) * D, g);
+    f32_load_cs<D, ROPE>(cs, p.table + (size_t)m * (D / 2), g);
+    f32_load_row<D>(dor, static_cast<const float*>(p.dout) + (bh * S + m) * D, g);
+    f32_load_t<D>(dot, static_cast<const float*>(p.dout) + bh * S * D, m0, S, lq, g);
 #pragma unroll
-        for (int d = 0; d < D; ++d) row[d] = Qf[tid][d];
-        rotate_row_f32<D, ROPE>(row, p.table + (size_t)(m0 + tid) * (D / 2));
-#pragma unroll
-        for (int d = 0; d < D; ++d) Qf[tid][d] = row[d];
-      }
-      __syncthreads();
-      if (!live) continue;
-      for (int i = 0; i < B32_BT; ++i) {
-        const int m = m0 + i;
-        bool ok = m < S;
-        if constexpr (MASK != MASK_NONE) ok = ok && (n <= m);
-        if constexpr (MASK == MASK_SLIDING_WINDOW) ok = ok && (n > m - W);
-        if (!ok) continue;
-        float s = 0.f, dp = 0.f;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-          s = __builtin_fmaf(k[d], Qf[i][d], s);
-          dp = __builtin_fmaf(vv[d], Of[i][d], dp);
-        }
-        const float x = ALIBI ? __builtin_fmaf(s, c2, slope2 * (float)(n - m)) : s * c2;
-        const float pr = exp2f(x - Lf[i]);
-        const float ds = pr * (dp - Df[i]);
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-          dv[d] = __builtin_fmaf(pr, Of[i][d], dv[d]);
-          dk[d] = __builtin_fmaf(ds, Qf[i][d], dk[d]);
-        }
-      }
+    for (int r = 0; r < 4; ++r) {
+      const size_t i = bh * S + min(m0 + 4 * g + r, S - 1);
+      l4[r] = p.lse[i];
+      d4[r] = p.delta[i];
     }
+  };
+  int it = wave;
+  if (it < items) load(it);
+  float k[DL], v[DL];
+  {
+    float x[DL];
+    f32_load_row<D>(k, static_cast<const float*>(p.k) + ((size_t)bg * S + nc) * D, g);
+    f32_load_cs<D, ROPE>(x, p.table + (size_t)nc * (D / 2), g);
+    f32_rotate<D, ROPE>(k, x);
+    f32_load_row<D>(v, static_cast<const float*>(p.v) + ((size_t)bg * S + nc) * D, g);
   }
-  if (!live) return;
+
+  f32x4 dk[MT], dv[MT];
 #pragma unroll
-  for (int d = 0; d < D; ++d) dk[d] *= p.scale;
-  if (ROPE != ROPE_NONE) rotate_row_f32<D, ROPE, true>(dk, p.table + (size_t)n * (D / 2));
-  float* dK = static_cast<float*>(p.dk) + ((size_t)bg * S + n) * D;
-  float* dV = static_cast<float*>(p.dv) + ((size_t)bg * S + n) * D;
+  for (int i = 0; i < MT; ++i) dk[i] = dv[i] = f32x4{};
+  for (; it < items; it += F32_NW) {
+    const int m0 = (tq + it % nt) * F32_T + 4 * g;   // query of element 0
+    const float slope2 = ALIBI ? p.slopes[h0 + it / nt] * kLog2e : 0.f;
+    float qr[DL], od[DL], ot[DL], qt[DL], l2[4], dl[4];
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    dK[d] = dk[d];
-    dV[d] = dv[d];
+    for (int i = 0; i < DL; ++i) {
+      qr[i] = q[i];
+      od[i] = dor[i];
+      ot[i] = dot[i];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      l2[r] = (l4[r] == -INFINITY) ? INFINITY : l4[r] * kLog2e;
+      dl[r] = d4[r];
+    }
+    f32_rotate<D, ROPE>(qr, cs);
+    if (it + F32_NW < items) load(it + F32_NW);
+    f32_transpose<D>(qt, qr, lds + wave * F32_T * (D + 4), lq, g);
+    const f32x4 s = f32_dot<D>(qr, k), dp = f32_dot<D>(od, v);
+    float pr[4], ds[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + r;
+      bool ok = n < S && m < S;
+      if constexpr (MASK != MASK_NONE) ok = ok && (n <= m);
+      if constexpr (MASK == MASK_SLIDING_WINDOW) ok = ok && (n > m - W);
+      const float x = ALIBI ? __builtin_fmaf(s[r], c2, slope2 * (float)(n - m)) : s[r] * c2;
+      pr[r] = ok ? exp2f(x - l2[r]) : 0.f;
+      ds[r] = ok ? pr[r] * (dp[r] - dl[r]) : 0.f;
+    }
+    f32_accumulate<D>(dv, ot, pr);
+    f32_accumulate<D>(dk, qt, ds);
+  }
+
+  const float one[F32_NW] = {1.f, 1.f, 1.f, 1.f}, sc[F32_NW] = {p.scale, p.scale, p.scale, p.scale};
+  const size_t out_row = ((size_t)bg * S + nc) * D;
+  const bool store = wave < D / 32 && n < S;
+  f32x4 out[2];
+  __syncthreads();   // every wave is past its transposition tile
+  f32_put<D>(lds, dk, wave, lane);
+  __syncthreads();
+  if (store) {
+    f32_get<D>(out, lds, sc, wave, lane);
+    f32_rotate_back<D, ROPE>(out, p.table + (size_t)n * (D / 2), wave, g);
+    f32_store<D>(static_cast<float*>(p.dk) + out_row, out, wave, g);
+  }
+  __syncthreads();
+  f32_put<D>(lds, dv, wave, lane);
+  __syncthreads();
+  if (store) {
+    f32_get<D>(out, lds, one, wave, lane);
+    f32_store<D>(static_cast<float*>(p.dv) + out_row, out, wave, g);
   }
 }
 
 template <int D, int ROPE, int MASK, bool ALIBI>
 static int launch_one(const BwdParams& p, hipStream_t st) {
-  const long long rows = (long long)p.B * p.H * p.S;
-  hipLaunchKernelGGL(bwd_fp32_prep_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, p, D);
-  const int nb = (p.S + B32_ROWS - 1) / B32_ROWS;
-  hipLaunchKernelGGL((bwd_fp32_dkdv_kernel<D, ROPE, MASK, ALIBI>), dim3((unsigned)(nb * p.B * p.Hkv)), dim3(B32_ROWS),
+  const int nb = (p.S + F32_T - 1) / F32_T;
+  hipLaunchKernelGGL((bwd_fp32_dq_kernel<D, ROPE, MASK, ALIBI>), dim3((unsigned)(nb * p.B * p.H)), dim3(64 * F32_NW),
                      0, st, p);
-  hipLaunchKernelGGL((bwd_fp32_dq_kernel<D, ROPE, MASK, ALIBI>), dim3((unsigned)(nb * p.B * p.H)), dim3(B32_ROWS), 0,
-                     st, p);
+  // after the dQ pass, which wrote delta
+  hipLaunchKernelGGL((bwd_fp32_dkdv_kernel<D, ROPE, MASK, ALIBI>), dim3((unsigned)(nb * p.B * p.Hkv)),
+                     dim3(64 * F32_NW), 0, st, p);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 

@@ -1,115 +1,137 @@
 // fp32 debug forward: the same method as the bf16 MFMA kernel (RoPE on the
-// query once and on every staged key tile, post-matmul modifications, online
-// softmax over key tiles, masked tiles skipped) in plain fp32 FMA arithmetic,
-// one query row per thread.  It exists to check the method at fp32 precision,
-// not for speed.
-#include "common.hpp"
+// query once and on every key tile, post-matmul modifications, online softmax
+// over key tiles, masked tiles skipped) in fp32 arithmetic throughout.
+//
+// One workgroup per 16 query rows; its waves take every F32_NW-th 16-key tile
+// and merge their (max, sum, O) at the end (fp32_tiles.hpp).  Debug shapes are
+// short, so what bounds it is the latency of the longest wave's chain of
+// tiles; each tile's K, V and table loads are issued one tile ahead.
+// Against one query row per thread of 64 with broadcast LDS reads: B1 H2 S128
+// D64 (interleaved, causal) 95 -> 7.6 us; B1 H32/8 S2048 D128 (NeoX, causal)
+// 9.4 -> 0.91 ms.
+#include "fp32_tiles.hpp"
 #include "launch.hpp"
 
 namespace af {
 
-constexpr int F32_ROWS = 64;   // query rows per workgroup (one wave)
-constexpr int F32_BN = 32;     // keys per tile
-
 template <int D, int ROPE, int MASK, bool ALIBI>
-__global__ __launch_bounds__(64) void fwd_fp32_kernel(FwdParams p) {
-  __shared__ float Kf[F32_BN][D + 1];
-  __shared__ float Vf[F32_BN][D + 1];
-  const int tid = threadIdx.x;
+__global__ __launch_bounds__(64 * F32_NW) void fwd_fp32_kernel(FwdParams p) {
+  constexpr int DL = D / 4, MT = D / 16;
+  __shared__ __attribute__((aligned(16))) float xch[F32_XCH<D>];
+  __shared__ float stat[2][F32_NW][16];
+  const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = p.S;
   const int BH = p.B * p.H;
-  const int nqb = (S + F32_ROWS - 1) / F32_ROWS;
+  const int nqb = (S + F32_T - 1) / F32_T;
   const int bh = blockIdx.x % BH;
-  const int qb = nqb - 1 - (int)(blockIdx.x / BH);
+  const int qb = nqb - 1 - (int)(blockIdx.x / BH);   // the longest causal rows first
   const int b = bh / p.H, h = bh % p.H;
-  const int g = h / (p.H / p.Hkv);
-  const int m0 = qb * F32_ROWS;
-  const int m = m0 + tid;
+  const size_t kv = (size_t)(b * p.Hkv + h / (p.H / p.Hkv)) * S * D;
+  const int m0 = qb * F32_T, m = m0 + lq, mc = min(m, S - 1);
   const float* __restrict__ Q = static_cast<const float*>(p.q) + (size_t)bh * S * D;
-  const float* __restrict__ K = static_cast<const float*>(p.k) + (size_t)(b * p.Hkv + g) * S * D;
-  const float* __restrict__ V = static_cast<const float*>(p.v) + (size_t)(b * p.Hkv + g) * S * D;
-
-  float q[D], acc[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    q[d] = (m < S) ? Q[(size_t)m * D + d] : 0.f;
-    acc[d] = 0.f;
-  }
-  if (ROPE != ROPE_NONE && m < S) rotate_row_f32<D, ROPE>(q, p.table + (size_t)m * (D / 2));
+  const float* __restrict__ K = static_cast<const float*>(p.k) + kv;
+  const float* __restrict__ V = static_cast<const float*>(p.v) + kv;
 
   const float c2 = p.scale * kLog2e;
   const float slope2 = ALIBI ? p.slopes[h] * kLog2e : 0.f;
   const int W = p.window;
-  const int ntiles = (S + F32_BN - 1) / F32_BN;
-  int t_begin = 0, t_end = ntiles;
-  if constexpr (MASK != MASK_NONE) t_end = min(ntiles, (min(m0 + F32_ROWS, S) - 1) / F32_BN + 1);
-  if constexpr (MASK == MASK_SLIDING_WINDOW) t_begin = max(0, m0 - W + 1) / F32_BN;
+  int t = wave, t_end = nqb;
+  if constexpr (MASK != MASK_NONE) t_end = qb + 1;
+  if constexpr (MASK == MASK_SLIDING_WINDOW) t += max(0, m0 - W + 1) / F32_T;
 
-  float m_run = -INFINITY, l_run = 0.f;
-  for (int t = t_begin; t < t_end; ++t) {
-    const int n0 = t * F32_BN;
-    __syncthreads();
-    // Stage the tile: thread tid < F32_BN rotates key row n0 + tid.
-    for (int r = 0; r < F32_BN; ++r) {
+  float k[DL], cs[DL], vt[DL];   // the tile in flight; rows past S: row S-1, masked
+  auto load = [&](int tile) {
+    const int n = min(tile * F32_T + lq, S - 1);
+    f32_load_row<D>(k, K + (size_t)n * D, g);
+    f32_load_cs<D, ROPE>(cs, p.table + (size_t)n * (D / 2), g);
+    f32_load_t<D>(vt, V, tile * F32_T, S, lq, g);
+  };
+  if (t < t_end) load(t);
+  float q[DL];
+  {
+    float qc[DL];
+    f32_load_row<D>(q, Q + (size_t)mc * D, g);
+    f32_load_cs<D, ROPE>(qc, p.table + (size_t)mc * (D / 2), g);
+    f32_rotate<D, ROPE>(q, qc);
+  }
+
+  f32x4 acc[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i] = f32x4{};
+  float m_run = -INFINITY, l_run = 0.f;   // l_run: this lane's part
+  for (; t < t_end; t += F32_NW) {
+    const int n0 = t * F32_T + 4 * g;     // key of element 0
+    float kr[DL], v[DL];
+#pragma unroll
+    for (int i = 0; i < DL; ++i) {
+      kr[i] = k[i];
+      v[i] = vt[i];
+    }
+    f32_rotate<D, ROPE>(kr, cs);
+    if (t + F32_NW < t_end) load(t + F32_NW);
+    const f32x4 s = f32_dot<D>(kr, q);
+    float x[4], mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
       const int n = n0 + r;
-      for (int d = tid; d < D; d += 64) {
-        Kf[r][d] = (n < S) ? K[(size_t)n * D + d] : 0.f;
-        Vf[r][d] = (n < S) ? V[(size_t)n * D + d] : 0.f;
-      }
-    }
-    __syncthreads();
-    if (ROPE != ROPE_NONE && tid < F32_BN && n0 + tid < S) {
-      float row[D];
-#pragma unroll
-      for (int d = 0; d < D; ++d) row[d] = Kf[tid][d];
-      rotate_row_f32<D, ROPE>(row, p.table + (size_t)(n0 + tid) * (D / 2));
-#pragma unroll
-      for (int d = 0; d < D; ++d) Kf[tid][d] = row[d];
-    }
-    __syncthreads();
-    if (m >= S) continue;
-
-    float sc[F32_BN];
-    float mx = -INFINITY;
-    for (int j = 0; j < F32_BN; ++j) {
-      const int n = n0 + j;
-      float dot = 0.f;
-#pragma unroll
-      for (int d = 0; d < D; ++d) dot = __builtin_fmaf(q[d], Kf[j][d], dot);
-      float x = ALIBI ? __builtin_fmaf(dot, c2, slope2 * (float)(n - m)) : dot * c2;
+      x[r] = ALIBI ? __builtin_fmaf(s[r], c2, slope2 * (float)(n - m)) : s[r] * c2;
       bool ok = n < S;
       if constexpr (MASK != MASK_NONE) ok = ok && (n <= m);
       if constexpr (MASK == MASK_SLIDING_WINDOW) ok = ok && (n > m - W);
-      sc[j] = ok ? x : -INFINITY;
-      mx = fmaxf(mx, sc[j]);
+      x[r] = ok ? x[r] : -INFINITY;
+      mx = fmaxf(mx, x[r]);
     }
-    const float m_new = fmaxf(m_run, mx);
+    const float m_new = fmaxf(m_run, groups_max(mx));
     const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
     const float alpha = exp2f(m_run - m_use);
     l_run *= alpha;
 #pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] *= alpha;
-    for (int j = 0; j < F32_BN; ++j) {
-      const float pj = exp2f(sc[j] - m_use);
-      l_run += pj;
+    for (int i = 0; i < MT; ++i) acc[i] *= alpha;
+    float pr[4];
 #pragma unroll
-      for (int d = 0; d < D; ++d) acc[d] = __builtin_fmaf(pj, Vf[j][d], acc[d]);
+    for (int r = 0; r < 4; ++r) {
+      pr[r] = exp2f(x[r] - m_use);
+      l_run += pr[r];
     }
+    f32_accumulate<D>(acc, v, pr);
     m_run = m_new;
   }
-  if (m < S) {
-    const float inv = (l_run > 0.f) ? 1.f / l_run : 0.f;
-    float* O = static_cast<float*>(p.o) + ((size_t)bh * S + m) * D;
+
+  f32_put<D>(xch, acc, wave, lane);
+  l_run = groups_sum(l_run);
+  if (g == 0) {
+    stat[0][wave][lq] = m_run;
+    stat[1][wave][lq] = l_run;
+  }
+  __syncthreads();
+  if (wave < D / 32) {
+    float w[F32_NW], mt = -INFINITY, l = 0.f;
 #pragma unroll
-    for (int d = 0; d < D; ++d) O[d] = acc[d] * inv;
-    p.lse[(size_t)bh * S + m] = (l_run > 0.f) ? (m_run + log2f(l_run)) * kLn2 : -INFINITY;
+    for (int j = 0; j < F32_NW; ++j) mt = fmaxf(mt, stat[0][j][lq]);
+    const float m_use = (mt == -INFINITY) ? 0.f : mt;
+#pragma unroll
+    for (int j = 0; j < F32_NW; ++j) {
+      w[j] = exp2f(stat[0][j][lq] - m_use);
+      l = __builtin_fmaf(stat[1][j][lq], w[j], l);
+    }
+    const float inv = (l > 0.f) ? 1.f / l : 0.f;
+    f32x4 o[2];
+    f32_get<D>(o, xch, w, wave, lane);
+    if (m < S) {
+      o[0] *= inv;
+      o[1] *= inv;
+      f32_store<D>(static_cast<float*>(p.o) + ((size_t)bh * S + m) * D, o, wave, g);
+      if (wave == 0 && g == 0) p.lse[(size_t)bh * S + m] = (l > 0.f) ? (mt + log2f(l)) * kLn2 : -INFINITY;
+    }
   }
 }
 
 template <int D, int ROPE, int MASK, bool ALIBI>
 static int launch_one(const FwdParams& p, hipStream_t st) {
-  const int nqb = (p.S + F32_ROWS - 1) / F32_ROWS;
-  hipLaunchKernelGGL((fwd_fp32_kernel<D, ROPE, MASK, ALIBI>), dim3((unsigned)(nqb * p.B * p.H)), dim3(64), 0, st, p);
+  const int nqb = (p.S + F32_T - 1) / F32_T;
+  hipLaunchKernelGGL((fwd_fp32_kernel<D, ROPE, MASK, ALIBI>), dim3((unsigned)(nqb * p.B * p.H)), dim3(64 * F32_NW),
+                     0, st, p);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
