@@ -4,6 +4,10 @@ Each function takes torch tensors that already live on the GPU, checks their
 shape/dtype/contiguity against the call, passes raw device pointers and the
 current torch stream to the library, and raises AttnFuseError on a non-zero
 return code.  Every step of the computation runs in the HIP kernels.
+
+Plain calls are marshalled by native/binding.cpp, which does the same checks;
+it declines (returns None) whatever it does not recognise, and the Python code
+after it then marshals the call or raises.
 """
 import functools
 import math
@@ -12,6 +16,11 @@ import numpy as np
 import torch
 
 from . import _lib
+
+try:   # the native half of this module: the same calls with their marshalling in C++
+    from . import _native
+except ImportError:   # not built for this interpreter: every call is marshalled below
+    _native = None
 
 DTYPE = {torch.bfloat16: 0, torch.float32: 1}
 ROPE = {"none": 0, "neox": 1, "interleaved": 2}
@@ -28,6 +37,13 @@ class AttnFuseError(RuntimeError):
 def _check(code, where):
     if code != 0:
         raise AttnFuseError(code, where)
+
+
+def _result(r, where):
+    """The outputs of a native call, which returns the library's code when that is not 0."""
+    if type(r) is int:
+        raise AttnFuseError(r, where)
+    return r
 
 
 def _ptr(t):
@@ -198,6 +214,11 @@ def _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, blocks=0):
 def attnfuse_fwd(q, k, v, *, rope="none", theta=10000.0, mask="causal", window=None,
                  alibi_slopes=None, scale=None, out=None, lse=None, rope_table=None):
     """O, LSE = attention(q, k, v); see attnfuse_fwd in include/attnfuse.h."""
+    if _native is not None:
+        r = _native.fwd(q, k, v, out, lse, alibi_slopes, rope_table, _TABLES, ROPE.get(rope, -1), theta,
+                        MASK.get(mask, -1), window, scale, 0, 0, 0, 0, 0, 0, 0, 0)
+        if r is not None:
+            return _result(r, "attnfuse_fwd")
     dev = _device(q)
     B, H, Hkv, S, D = _shape(q, k)
     _inputs(q, k, v, dev)
@@ -227,6 +248,11 @@ def attnfuse_bwd_workspace_bytes(B, H, H_kv, S, D, rope="none"):
 def attnfuse_bwd(q, k, v, o, do, lse, *, rope="none", theta=10000.0, mask="causal", window=None,
                  alibi_slopes=None, scale=None, dq=None, dk=None, dv=None, workspace=None, rope_table=None):
     """dQ, dK, dV of attnfuse_fwd; see attnfuse_bwd in include/attnfuse.h."""
+    if _native is not None:
+        r = _native.bwd(q, k, v, o, do, lse, dq, dk, dv, workspace, alibi_slopes, rope_table, _TABLES,
+                        ROPE.get(rope, -1), theta, MASK.get(mask, -1), window, scale, 0, 0, 0, 0, 0, 0, 0, 0, 0)
+        if r is not None:
+            return _result(r, "attnfuse_bwd")
     dev = _device(q)
     B, H, Hkv, S, D = _shape(q, k)
     _bwd_inputs(q, k, v, o, do, lse, dev, lse_needed=True)
@@ -268,12 +294,18 @@ def attnfuse_fwd_blocksparse(q, k, v, block_mask, *, rope="none", theta=10000.0,
     B, H, Hkv, S, D = _shape(q, k)
     _inputs(q, k, v, dev)
     qp, ki, _, _ = _mask_ptrs(block_mask, q, S)
+    blocks = max(1, block_mask.k_idx.numel())
+    if _native is not None:
+        r = _native.fwd(q, k, v, out, lse, alibi_slopes, rope_table, _TABLES, ROPE.get(rope, -1), theta,
+                        MASK.get(mask, -1), window, scale, 0, 0, 0, 0, 0, qp, ki, blocks)
+        if r is not None:
+            return _result(r, "attnfuse_fwd_blocksparse")
     out = _opt(out, "out", q.shape, q.dtype, dev)
     lse = _opt(lse, "lse", (B, H, S), torch.float32, dev)
     r, th, m, w, sc = _variant(rope, theta, mask, window, alibi_slopes, scale, D, H, dev)
     tab = _table(rope, theta, D, S, dev, rope_table)
     tp, tr = _tab(tab)
-    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, max(1, block_mask.k_idx.numel()))
+    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, blocks)
     with torch.cuda.device(dev):
         if ws is not None:
             code = _lib.load().af_fwd_ws(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), qp, ki, None, 0, 0, 0, 0,
@@ -296,6 +328,11 @@ def attnfuse_bwd_blocksparse(q, k, v, o, do, lse, block_mask, *, rope="none", th
     B, H, Hkv, S, D = _shape(q, k)
     _bwd_inputs(q, k, v, o, do, lse, dev, lse_needed=True)
     qp, ki, kp, qi = _mask_ptrs(block_mask, q, S)
+    if _native is not None:
+        r = _native.bwd(q, k, v, o, do, lse, dq, dk, dv, workspace, alibi_slopes, rope_table, _TABLES,
+                        ROPE.get(rope, -1), theta, MASK.get(mask, -1), window, scale, 0, 0, 0, 0, 0, qp, ki, kp, qi)
+        if r is not None:
+            return _result(r, "attnfuse_bwd_blocksparse")
     dq, dk, dv = _grads(q, k, dq, dk, dv, dev)
     workspace, wbytes = _workspace(workspace, attnfuse_bwd_workspace_bytes(B, H, Hkv, S, D, rope), dev)
     r, th, m, w, sc = _variant(rope, theta, mask, window, alibi_slopes, scale, D, H, dev)
@@ -334,6 +371,12 @@ def attnfuse_fwd_bias_norm(q, k, v, *, bias=None, norm="softmax", rope="none", t
     relu attention; see attnfuse_fwd_bias_norm in include/attnfuse.h."""
     dev = _device(q)
     B, H, Hkv, S, D = _shape(q, k)
+    if _native is not None:
+        r = _native.fwd(q, k, v, out, lse, None, rope_table, _TABLES, ROPE.get(rope, -1), theta, MASK.get(mask, -1),
+                        window, scale, *_bias_args(bias, q, B, H, S), NORM.get(norm, -1),
+                        0, 0, 0)
+        if r is not None:
+            return _result(r, "attnfuse_fwd_bias_norm")
     _inputs(q, k, v, dev)
     out = _opt(out, "out", q.shape, q.dtype, dev)
     if NORM[norm] == NORM["softmax"] or lse is not None:
@@ -364,6 +407,12 @@ def attnfuse_bwd_bias_norm(q, k, v, o, do, lse, *, bias=None, norm="softmax", ro
     attention); see attnfuse_bwd_bias_norm."""
     dev = _device(q)
     B, H, Hkv, S, D = _shape(q, k)
+    if _native is not None:
+        r = _native.bwd(q, k, v, o, do, lse, dq, dk, dv, workspace, None, rope_table, _TABLES, ROPE.get(rope, -1),
+                        theta, MASK.get(mask, -1), window, scale, *_bias_args(bias, q, B, H, S), NORM.get(norm, -1),
+                        0, 0, 0, 0)
+        if r is not None:
+            return _result(r, "attnfuse_bwd_bias_norm")
     _bwd_inputs(q, k, v, o, do, lse, dev, lse_needed=NORM[norm] == NORM["softmax"])
     dq, dk, dv = _grads(q, k, dq, dk, dv, dev)
     workspace, wbytes = _workspace(workspace, attnfuse_bwd_workspace_bytes(B, H, Hkv, S, D, rope), dev)
@@ -407,6 +456,11 @@ def attnfuse_decode(q, k_cache, v_cache, cache_lens=None, *, rope="none", theta=
                     rope_table=None):
     """O [B,H,D], LSE [B,H] of one query per sequence against a KV cache of
     already-rotated keys; see attnfuse_decode in include/attnfuse.h."""
+    if _native is not None:
+        r = _native.decode(q, k_cache, v_cache, cache_lens, out, lse, workspace, alibi_slopes, rope_table, _TABLES,
+                           ROPE.get(rope, -1), theta, MASK.get(mask, -1), window, scale, 0)
+        if r is not None:
+            return _result(r, "attnfuse_decode")
     dev, (B, H, Hkv, S_kv, D), out, lse = _decode_args(q, k_cache, v_cache, cache_lens, out, lse)
     workspace, wbytes = _workspace(workspace, attnfuse_decode_workspace_bytes(B, H, Hkv, S_kv, D), dev)
     r, th, m, w, sc = _variant(rope, theta, mask, window, alibi_slopes, scale, D, H, dev)
@@ -426,6 +480,11 @@ def attnfuse_decode_noalloc(q, k_cache, v_cache, cache_lens=None, *, rope="none"
     workspace; see attnfuse_decode_noalloc in include/attnfuse.h.  Pass
     ``out``, ``lse`` (and, with RoPE, ``rope_table``) for a call that
     allocates nothing at all."""
+    if _native is not None:
+        r = _native.decode(q, k_cache, v_cache, cache_lens, out, lse, None, alibi_slopes, rope_table, _TABLES,
+                           ROPE.get(rope, -1), theta, MASK.get(mask, -1), window, scale, 1)
+        if r is not None:
+            return _result(r, "attnfuse_decode_noalloc")
     dev, (B, H, Hkv, S_kv, D), out, lse = _decode_args(q, k_cache, v_cache, cache_lens, out, lse)
     r, th, m, w, sc = _variant(rope, theta, mask, window, alibi_slopes, scale, D, H, dev)
     tab = _table(rope, theta, D, S_kv, dev, rope_table)
@@ -439,6 +498,11 @@ def attnfuse_decode_noalloc(q, k_cache, v_cache, cache_lens=None, *, rope="none"
 
 
 def _rope_call(name, x0, x1, y0, y1, rope, theta, rope_table):
+    if _native is not None:
+        r = _native.rope(x0, x1, y0, y1, rope_table, _TABLES, ROPE.get(rope, -1), theta,
+                         int(name == "attnfuse_rope_bwd"))
+        if r is not None:
+            return _result(r, name)
     dev = _device(x0)
     if x1 is not None:
         B, H, Hkv, S, D = _shape(x0, x1)

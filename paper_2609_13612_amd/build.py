@@ -1,4 +1,5 @@
-"""Build lib/libattnfuse.so from csrc/ with hipcc for gfx950.
+"""Build lib/libattnfuse.so from csrc/ with hipcc for gfx950, and the binding's
+native half, _native.so, from native/.
 
 Usage: python -m paper_2609_13612_amd.build [-j N]
 
@@ -20,6 +21,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIBDIR = os.path.join(PKG, "lib")
 LIB = os.path.join(LIBDIR, "libattnfuse.so")
+NATIVE = os.path.join(PKG, "_native.so")
 
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -72,7 +74,24 @@ def build(jobs=None, verbose=False):
     if res.returncode != 0:
         raise RuntimeError(f"link failed:\n{res.stderr}")
     os.replace(tmp, LIB)
+    build_native()
     return LIB
+
+
+def build_native():
+    """Compile the binding's native half (host code only) against torch, next to the package's modules."""
+    import sysconfig
+    import torch
+    t = os.path.dirname(torch.__file__)
+    tmp = NATIVE + ".tmp"
+    cmd = [HIPCC, "-shared", "-fPIC", "-O2", "-std=c++17", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+           f"-I{t}/include", f"-I{t}/include/torch/csrc/api/include", f"-I{sysconfig.get_paths()['include']}",
+           f"-I{INCLUDE}", f"-I{CSRC}", os.path.join(PKG, "native", "binding.cpp"), "-o", tmp, f"-L{t}/lib", "-lc10",
+           "-lc10_hip", "-ltorch_cpu", "-ltorch_python", f"-L{LIBDIR}", "-lattnfuse", "-Wl,-rpath,$ORIGIN/lib"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"native binding failed:\n{res.stderr}")
+    os.replace(tmp, NATIVE)
 
 
 if __name__ == "__main__":

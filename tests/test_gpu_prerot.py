@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 def _both(monkeypatch, call, k):
     scratch = torch.empty(k.numel() * 2, dtype=torch.uint8, device="cuda")
     res = []
+    monkeypatch.setattr(api, "_native", None)   # marshalled where the scratch can be chosen
     for s in (None, scratch):
         monkeypatch.setattr(api, "_fwd_scratch", lambda *a, s=s, **kw: s)
         res.append(call())
