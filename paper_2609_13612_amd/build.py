@@ -30,7 +30,7 @@ DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", f"-I{INCLUDE}", f"-I{CSRC}",
           "-Wall", "-Wno-unused-function"]
 
-SOURCES = ["api.cpp", "rope.hip", "fwd_bf16.hip", "fwd_prerot.hip", "fwd_fp32.hip", "bwd_bf16.hip", "bwd_dkdv.hip", "bwd_fp32.hip",
+SOURCES = ["api.cpp", "rope.hip", "fwd_bf16.hip", "fwd_prerot.hip", "fwd_norope.hip", "fwd_fp32.hip", "bwd_bf16.hip", "bwd_dkdv.hip", "bwd_fp32.hip",
            "decode.hip"]
 # Code-generation options of single translation units.  The dK/dV kernels
 # run faster when the machine scheduler keeps its first schedule instead of

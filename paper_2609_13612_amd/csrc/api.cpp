@@ -323,16 +323,19 @@ int attnfuse_fwd_bias_norm(const void* Q, const void* K, const void* V, void* O,
 }
 
 // Rotating the keys once costs a launch and a pass over K (read bf16, write
-// fp16); rotating them in the loop costs every workgroup VALU work on every
-// tile it visits.  Measured on MI355X (the two forms in turn, eager calls):
-//   B1 H32/8 D128 causal S 512 / 1024 / 2048 / 4096 / 8192: in-loop 25.2 / 39.4 / 69.1 / 167 / 621 us, rotated once
-//   25.6 / 38.0 / 65.2 / 154 / 558 us; B4 H12 D64 no mask S 1024 / 2048 / 4096: 26.3 / 91.3 / 276 and 29.8 / 91.6 /
-//   261 us; B4 H32/8 S8192 window 1024: 763 and 688 us; block-sparse B4 H12 S4096 D64 (9.2 % active): 123 and 82 us.
-// These fit a launch of 2.6 us plus the pass at 4.5 TB/s against 0.27 us
-// (D = 128), 0.135 us (D = 64) or 0.6 us (block-sparse) for each tile that the
-// busiest CU rotates.  D = 64 loses below that line, so both forms stay.
+// fp16: 2.6 us and 4.5 TB/s); rotating them in the loop costs every workgroup
+// VALU work on every tile it visits, and keeps the tiles from being copied
+// straight to LDS.  Measured on MI355X, in the loop / rotated once, us:
+//   D = 128, H32/8 B1 causal, S 128 / 256 / 512 / 1024 / 2048 / 8192: 10.1 / 11.9, 14.6 / 13.9, 22.6 / 18.4,
+//   38.5 / 26.8, 67 / 53, 605 / 528; B4 S8192 window 1024: 772 / 626; B16 H16 S512: 50.5 / 53.5;
+//   D = 64, H12 B4 causal, S 512 / 1024 / 2048 / 4096: 13.4 / 15.7, 23.4 / 24.5, 48.5 / 49.5, 160 / 136; no mask 2048:
+//   89.6 / 73.5; window 256 at 4096: 58.5 / 47.1; B32 H16 S512: 58.5 / 55.2;
+//   block-sparse (9.2 % active) B4 H12 S4096 D64: 123 / 82; relu attention gains the rotation alone.
+// The saving follows the tiles of the longest workgroup while 256-row
+// workgroups leave CUs free, and otherwise the workgroups each CU takes in turn
+// (5 us each) and the tiles of the busiest CU.
 size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, int rope, int mask, int window,
-                              long long sparse_blocks) {
+                              int norm, long long sparse_blocks) {
   if (B < 1 || H < 1 || H_kv < 1 || S < 1 || S > kMaxS || H % H_kv || !supported_d(D) || dtype != AF_DTYPE_BF16 ||
       rope == AF_ROPE_NONE)
     return 0;
@@ -342,22 +345,22 @@ size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, i
   while (hp < (sparse_blocks ? 4 : 8) && G % (2 * hp) == 0) hp *= 2;
   const double units = (double)B * H_kv * (G / hp);
   const double nt = (S + 63) / 64;
-  double tiles, longest;            // key tiles visited per unit, and by the longest workgroup
+  double saved;
   if (sparse_blocks) {
-    tiles = (double)sparse_blocks * (mask == AF_MASK_NONE ? 1.0 : 0.5);
-    longest = 0;                    // shared by key groups
+    saved = 0.6 * units * (double)sparse_blocks * (mask == AF_MASK_NONE ? 1.0 : 0.5) / 256.0;
   } else {
     const double rows = 256.0 / hp, wgs = std::ceil(S / rows);
-    longest = nt;
-    tiles = wgs * nt;
+    double longest = nt, tiles = wgs * nt;   // key tiles of the longest workgroup, and of all of a unit's
     if (mask == AF_MASK_CAUSAL) tiles = wgs * (nt + rows / 64.0) / 2.0;
     if (mask == AF_MASK_SLIDING_WINDOW) {
       longest = std::fmin(nt, (rows + window) / 64.0 + 1.0);
       tiles = std::fmin(wgs * (nt + rows / 64.0) / 2.0, wgs * longest);
     }
+    const double turns = units * wgs / 256.0, load = std::fmax(longest, units * tiles / 256.0);
+    if (norm == AF_NORM_RELU) saved = (D == 128 ? 0.27 : 0.135) * load;
+    else if (turns <= 1.0) saved = (D == 128 ? 0.8 : 0.25) * longest;
+    else saved = 5.0 * (turns - 1.0) + (D == 128 ? 0.3 : 0.2) * load;
   }
-  const double per_tile = sparse_blocks ? 0.6 : (D == 128 ? 0.27 : 0.135);
-  const double saved = per_tile * std::fmax(longest, units * tiles / 256.0);
   return saved > 2.6 + (double)bytes * 2.0 / 4.5e6 ? bytes : 0;
 }
 

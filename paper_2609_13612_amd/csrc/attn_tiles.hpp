@@ -11,9 +11,9 @@
 
 namespace af {
 
-template <int D, int ROPE>
+template <int D, int ROPE, int NW_ = 8>
 struct TileCfg {
-  static constexpr int NW = 8;                 // waves per workgroup
+  static constexpr int NW = NW_;               // waves per workgroup
   static constexpr int THREADS = 64 * NW;
   static constexpr int ROWS = 32 * NW;         // query rows per workgroup
   static constexpr int BN = 64;                // keys per tile
@@ -39,9 +39,9 @@ struct TileCfg {
 
 // Registers holding one key tile between its global load and its LDS commit
 // (NeoX runs of 4 pairs travel as 8-byte halves).
-template <int D, int ROPE>
+template <int D, int ROPE, int NW = 8>
 struct TileRegs {
-  using C = TileCfg<D, ROPE>;
+  using C = TileCfg<D, ROPE, NW>;
   using KVec = std::conditional_t<C::KW == 4, u32x2, u32x4>;
   KVec ka[C::KPT];
   KVec kb[(ROPE == ROPE_NEOX) ? C::KPT : 1];
@@ -52,17 +52,17 @@ struct TileRegs {
 // Rows past S are clamped to row S-1 so every load is unconditional: those
 // keys are masked out of the scores and their V rows (finite data) receive
 // zero probability.  K and V halves can be loaded and committed separately.
-template <int D, int ROPE>
-__device__ __forceinline__ void tile_load_k(TileRegs<D, ROPE>& R, const uint16_t* __restrict__ K,
+template <int D, int ROPE, int NW>
+__device__ __forceinline__ void tile_load_k(TileRegs<D, ROPE, NW>& R, const uint16_t* __restrict__ K,
                                             const float2* __restrict__ table, int n0, int S, int tid) {
-  using C = TileCfg<D, ROPE>;
+  using C = TileCfg<D, ROPE, NW>;
 #pragma unroll
   for (int i = 0; i < C::KPT; ++i) {
     const int it = tid + C::THREADS * i;
     if (C::K_ITEMS % C::THREADS != 0 && it >= C::K_ITEMS) break;
     const int r = it / C::K_UNITS, c = it % C::K_UNITS, n = min(n0 + r, S - 1);
     if constexpr (ROPE == ROPE_NEOX) {
-      using KV = typename TileRegs<D, ROPE>::KVec;
+      using KV = typename TileRegs<D, ROPE, NW>::KVec;
       R.ka[i] = *reinterpret_cast<const KV*>(K + (size_t)n * D + C::KW * c);
       R.kb[i] = *reinterpret_cast<const KV*>(K + (size_t)n * D + D / 2 + C::KW * c);
       load_cs(R.cs[i], table + (size_t)n * (D / 2) + C::KW * c);
@@ -75,10 +75,10 @@ __device__ __forceinline__ void tile_load_k(TileRegs<D, ROPE>& R, const uint16_t
   }
 }
 
-template <int D, int ROPE>
-__device__ __forceinline__ void tile_load_v(TileRegs<D, ROPE>& R, const uint16_t* __restrict__ V, int n0, int S,
+template <int D, int ROPE, int NW>
+__device__ __forceinline__ void tile_load_v(TileRegs<D, ROPE, NW>& R, const uint16_t* __restrict__ V, int n0, int S,
                                             int tid) {
-  using C = TileCfg<D, ROPE>;
+  using C = TileCfg<D, ROPE, NW>;
 #pragma unroll
   for (int i = 0; i < C::VPT; ++i) {
     const int it = tid + C::THREADS * i;
@@ -88,8 +88,8 @@ __device__ __forceinline__ void tile_load_v(TileRegs<D, ROPE>& R, const uint16_t
   }
 }
 
-template <int D, int ROPE>
-__device__ __forceinline__ void tile_load(TileRegs<D, ROPE>& R, const uint16_t* __restrict__ K,
+template <int D, int ROPE, int NW>
+__device__ __forceinline__ void tile_load(TileRegs<D, ROPE, NW>& R, const uint16_t* __restrict__ K,
                                           const uint16_t* __restrict__ V, const float2* __restrict__ table,
                                           int n0, int S, int tid) {
   tile_load_k<D, ROPE>(R, K, table, n0, S, tid);
@@ -97,9 +97,9 @@ __device__ __forceinline__ void tile_load(TileRegs<D, ROPE>& R, const uint16_t* 
 }
 
 // Rotate the staged K rows and write K' (and, separately, V) into an LDS stage.
-template <int D, int ROPE>
-__device__ __forceinline__ void tile_commit_k(TileRegs<D, ROPE>& R, uint16_t* __restrict__ Ks, int tid) {
-  using C = TileCfg<D, ROPE>;
+template <int D, int ROPE, int NW>
+__device__ __forceinline__ void tile_commit_k(TileRegs<D, ROPE, NW>& R, uint16_t* __restrict__ Ks, int tid) {
+  using C = TileCfg<D, ROPE, NW>;
 #pragma unroll
   for (int i = 0; i < C::KPT; ++i) {
     const int it = tid + C::THREADS * i;
@@ -119,9 +119,9 @@ __device__ __forceinline__ void tile_commit_k(TileRegs<D, ROPE>& R, uint16_t* __
 }
 
 // V16: store V converted to fp16 (exact for |v| < 65504), for fp16 P operands.
-template <int D, int ROPE, bool V16 = false>
-__device__ __forceinline__ void tile_commit_v(const TileRegs<D, ROPE>& R, uint16_t* __restrict__ Vs, int tid) {
-  using C = TileCfg<D, ROPE>;
+template <int D, int ROPE, bool V16 = false, int NW>
+__device__ __forceinline__ void tile_commit_v(const TileRegs<D, ROPE, NW>& R, uint16_t* __restrict__ Vs, int tid) {
+  using C = TileCfg<D, ROPE, NW>;
 #pragma unroll
   for (int i = 0; i < C::VPT; ++i) {
     const int it = tid + C::THREADS * i;
@@ -136,12 +136,94 @@ __device__ __forceinline__ void tile_commit_v(const TileRegs<D, ROPE>& R, uint16
   }
 }
 
-template <int D, int ROPE, bool V16 = false>
-__device__ __forceinline__ void tile_commit(TileRegs<D, ROPE>& R, uint16_t* __restrict__ Ks,
+template <int D, int ROPE, bool V16 = false, int NW>
+__device__ __forceinline__ void tile_commit(TileRegs<D, ROPE, NW>& R, uint16_t* __restrict__ Ks,
                                             uint16_t* __restrict__ Vs, int tid) {
   tile_commit_k<D, ROPE>(R, Ks, tid);
   tile_commit_v<D, ROPE, V16>(R, Vs, tid);
 }
+
+// ---------------------------------------------------------------- tiles copied straight to LDS
+// A 64-row tile that needs no arithmetic on its way (rotated keys from the
+// workspace, V, unrotated K) goes from global memory to LDS without passing
+// through registers (global_load_lds): the waves issue the copies and the tile
+// is there after the wait and barrier that end the iteration.  That frees the
+// 16 staging registers and the LDS-write instructions of the register route
+// (Llama-3-8B forward 517 -> 494 us in one run) and makes staging cheap enough
+// that two workgroups per CU, each with its own tiles, beat one of twice the
+// rows on all but the longest sequences.
+//
+// One instruction of a wave fills 1 KB in lane order, so rows cannot be padded
+// one by one.  A group of 1 KB (4 rows at D = 128, 8 at D = 64) is followed by
+// 16 bytes, and inside it chunk c of row r (16 bytes) sits at slot c ^ f(r):
+// with 64 banks of 4 bytes, 16 rows of one chunk (ds_read_b128) and 64 bytes of
+// 4 rows (the transpose read) both fall on distinct banks.  f touches only the
+// chunk bits that the k-step (rows) or the column tile (transposed) counts in,
+// so four (or two) lane offsets and immediates address every read.
+__device__ __forceinline__ void async_copy16(const void* sbase, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds)
+               : "memory", "m0");
+}
+// Every copy this wave issued has landed (the barrier after it says so for all waves).
+__device__ __forceinline__ void async_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+template <int D, int NW>
+struct AsyncTile {
+  static constexpr int GROUP = 512 + 8;        // elements of a 1 KB group and its padding
+  static constexpr int RPG = 512 / D;          // rows per group
+  static constexpr int GROUPS = 64 / RPG;
+  static constexpr int ELEMS = GROUPS * GROUP;
+  static constexpr int NI = GROUPS / NW;       // groups each wave copies
+  static_assert(GROUPS % NW == 0, "every wave copies the same number of groups");
+  static constexpr int NK = 4, NV = D / 32;
+  int row0;             // this lane's row in the wave's first group
+  uint32_t col;         // and the byte offset of the chunk it copies
+  int wave;
+  int kb[NK], vb[NV];   // lane offsets of the row and the transposed reads
+
+  static __device__ __forceinline__ int f(int r) {
+    if constexpr (D == 128) return (r & 3) << 2;
+    else return (((r >> 1) & 1) << 2) | (((r >> 2) & 1) << 1);
+  }
+  static __device__ __forceinline__ int at(int r, int c) {   // element offset of chunk c of row r
+    return (r / RPG) * GROUP + (r % RPG) * D + ((c ^ f(r)) << 3);
+  }
+  __device__ __forceinline__ AsyncTile(int lane, int wave_) : wave(wave_) {
+    constexpr int CPR = D / 8;
+    const int r = lane / CPR;
+    row0 = RPG * wave + r;
+    col = (uint32_t)(((lane % CPR) ^ f(r)) << 4);
+    const int lq = lane & 31, lg = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < NK; ++j) kb[j] = at(lq, (D == 128 ? 4 * j : 2 * j) + lg);
+    const int tr = 4 * lg + ((lane & 15) >> 2);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) vb[j] = at(tr, 4 * j + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) + 4 * (lane & 1);
+  }
+  // Copy rows n0 .. n0 + 63 of X (rows past S: row S - 1; n0 < S) to the stage dst.
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ X, int n0, int S, uint16_t* dst) const {
+    const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)dst;
+    const uint16_t* base = X + (size_t)n0 * D;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int r = min(row0 + NW * RPG * i, S - 1 - n0);
+      async_copy16(base, (uint32_t)r * (2 * D) + col,
+                   __builtin_amdgcn_readfirstlane(lds + (wave + NW * i) * (GROUP * 2)));
+    }
+  }
+  // MFMA operands: row r0 + l % 32, k-step k; and rows r0 + {4 (l / 32) + .., +8},
+  // column tile mt, transposed (r0 a multiple of 16).
+  __device__ __forceinline__ u32x4 row(const uint16_t* t, int r0, int k) const {
+    const int j = D == 128 ? k >> 1 : k, e = D == 128 ? 16 * (k & 1) : 0;
+    return *reinterpret_cast<const u32x4*>(t + kb[j] + (r0 / RPG) * GROUP + e);
+  }
+  __device__ __forceinline__ u32x4 tr(const uint16_t* t, int r0, int mt) const {
+    const uint16_t* p = t + vb[mt] + (r0 / RPG) * GROUP;
+    const u32x2 lo = lds_read_tr16(p);
+    const u32x2 hi = lds_read_tr16(p + (8 / RPG) * GROUP);
+    return u32x4{lo[0], lo[1], hi[0], hi[1]};
+  }
+};
 
 // ---------------------------------------------------------------- output rows
 // Store a wave's 32 rows of a bf16 output held as MFMA accumulators (lane

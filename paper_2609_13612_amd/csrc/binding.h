@@ -16,7 +16,7 @@ extern "C" {
  * rotated once into it), or 0 where it is better without.  sparse_blocks: the
  * active blocks of a block mask, 0 without one. */
 size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, int rope, int mask, int window,
-                              long long sparse_blocks);
+                              int norm, long long sparse_blocks);
 
 /* attnfuse_fwd (bias == NULL, q_block_ptr == NULL), attnfuse_fwd_bias_norm or
  * attnfuse_fwd_blocksparse with RoPE on bf16 tensors, given

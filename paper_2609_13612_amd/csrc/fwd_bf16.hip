@@ -5,9 +5,12 @@
 namespace af {
 
 template <int D>
+int launch_fwd_norope(int mask, bool alibi, int ext, const FwdParams& p, hipStream_t st);   // fwd_norope.hip
+
+template <int D>
 static int dispatch_rope(int rope, int mask, bool alibi, int ext, const FwdParams& p, hipStream_t st) {
   switch (rope) {
-    case ROPE_NONE: return fwd_dispatch_mask<D, ROPE_NONE, false>(mask, alibi, ext, p, st);
+    case ROPE_NONE: return launch_fwd_norope<D>(mask, alibi, ext, p, st);
     case ROPE_NEOX: return fwd_dispatch_mask<D, ROPE_NEOX, false>(mask, alibi, ext, p, st);
     case ROPE_INTERLEAVED: return fwd_dispatch_mask<D, ROPE_INTERLEAVED, false>(mask, alibi, ext, p, st);
   }

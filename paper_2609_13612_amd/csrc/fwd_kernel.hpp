@@ -8,8 +8,8 @@
 // masked key tiles are never visited.
 //
 // Work decomposition
-//   workgroup = 8 waves (two per SIMD) = 256 query rows.  The rows are HP
-//   query heads of one GQA group x 256/HP positions, so one rotated K tile
+//   workgroup = NW waves (8 or 4) = 32 NW query rows.  The rows are HP
+//   query heads of one GQA group x 32 NW / HP positions, so one rotated K tile
 //   serves every head that reads it.  Each wave owns 32 query rows and walks
 //   the key tiles (BN = 64 keys) as a two-stage software pipeline with one
 //   barrier per tile: part A issues tile t+1's score MFMAs while the VALU
@@ -46,11 +46,22 @@
 
 namespace af {
 
-template <int D, int ROPE, int MASK, bool ALIBI, bool SPARSE, int EXT = EXT_NONE, bool KPRE = false>
-__global__ __launch_bounds__(512) void fwd_bf16_kernel(FwdParams p) {
+// Waves per SIMD the registers are held to: three of a 4-wave workgroup fit at
+// D = 64 when the tiles need no registers (168 each; B8 H16 S2048 causal 106 ->
+// 97 us against two), two otherwise (relu attention stages through registers,
+// and a window with a bias or slopes would spill).
+template <int D, int ROPE, int MASK, bool ALIBI, int EXT, bool KPRE, int NW>
+constexpr int FWD_WAVES = (D == 64 && NW == 4 && (KPRE || ROPE == ROPE_NONE) && (EXT == EXT_NONE || EXT == EXT_BIAS) &&
+                           !(MASK == MASK_SLIDING_WINDOW && (ALIBI || EXT == EXT_BIAS)))
+                              ? 3
+                              : 2;
+
+template <int D, int ROPE, int MASK, bool ALIBI, bool SPARSE, int EXT, bool KPRE, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(FWD_WAVES<D, ROPE, MASK, ALIBI, EXT, KPRE, NW>)))
+void fwd_bf16_kernel(FwdParams p) {
   static_assert(!KPRE || ROPE != ROPE_NONE, "only rotated keys come from the workspace");
   constexpr int KROPE = KPRE ? ROPE_NONE : ROPE;   // rotation of the key tiles as they are staged
-  using C = TileCfg<D, KROPE>;
+  using C = TileCfg<D, KROPE, NW>;
   constexpr bool QF16 = ROPE != ROPE_NONE;
   constexpr bool TBIAS = EXT == EXT_BIAS || EXT == EXT_RELU_BIAS;   // dense bias tensor
   constexpr bool RELU = EXT == EXT_RELU || EXT == EXT_RELU_BIAS;    // P = max(s, 0), unnormalised
@@ -58,7 +69,13 @@ __global__ __launch_bounds__(512) void fwd_bf16_kernel(FwdParams p) {
   constexpr bool PRESCALED = ALIBI || TBIAS || RELU;
   // Relu weights are unnormalised (not bounded by 1): P and V go to the PV
   // MFMA as fp16 (2^-12 rounding of P instead of bf16's 2^-9).
-  __shared__ __attribute__((aligned(16))) uint16_t smem[(SPARSE ? 4 : 2) * C::STAGE];
+  // tiles that need no arithmetic on their way to LDS are copied there
+  // directly (relu attention converts V; block-sparse keeps its register sets)
+  constexpr bool ASYNC = KROPE == ROPE_NONE && !SPARSE && !RELU;
+  using AT = AsyncTile<D, NW>;
+  constexpr int STAGES = ASYNC ? 4 * AT::ELEMS : (SPARSE ? 4 : 2) * C::STAGE;
+  constexpr int OUT = NW * OUT_ROWS_ELEMS<D>;   // the output rows leave through the same memory
+  __shared__ __attribute__((aligned(16))) uint16_t smem[STAGES > OUT ? STAGES : OUT];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -132,6 +149,17 @@ __global__ __launch_bounds__(512) void fwd_bf16_kernel(FwdParams p) {
   auto kst = [&](int X) { return smem + __builtin_amdgcn_readfirstlane(SPARSE ? X : (X & 1)) * C::STAGE; };
   auto vst = [&](int X) { return kst(X) + C::K_ELEMS; };
 
+  // The first tiles copied to LDS are in flight while the query is loaded:
+  // K' of tiles 0 and 1, V of tile 0.  Stage X & 1 holds tile X.
+  const AT at(lane, wave);
+  auto akst = [&](int par) { return smem + 2 * par * AT::ELEMS; };
+  auto avst = [&](int par) { return smem + (2 * par + 1) * AT::ELEMS; };
+  if constexpr (ASYNC) {
+    at.load(K, tile_at(0) * C::BN, S, akst(0));
+    at.load(V, tile_at(0) * C::BN, S, avst(0));
+    if (1 < ntl) at.load(K, tile_at(1) * C::BN, S, akst(1));
+  }
+
   // Query operand (B of S^T = K Q^T): lane holds row m, dims 16s + 8lg .. +7.
   // Rows past S load row S-1 (finite data; never stored).
   const int mc = min(m, S - 1);
@@ -155,8 +183,10 @@ __global__ __launch_bounds__(512) void fwd_bf16_kernel(FwdParams p) {
 
   // Prologue: stage K' of the first two tiles and V of the first; load the
   // registers of the first in-loop commit (K' of the third, V of the second).
-  TileRegs<D, KROPE> R;
-  if constexpr (!SPARSE) {
+  TileRegs<D, KROPE, NW> R;
+  if constexpr (ASYNC) {
+    async_wait();
+  } else if constexpr (!SPARSE) {
     for (int X = 0; X < min(2, ntl); ++X) {
       tile_load<D, KROPE>(R, K, V, p.table, tile_at(X) * C::BN, S, tid);
       tile_commit_k<D, KROPE>(R, kst(X), tid);
@@ -194,7 +224,9 @@ __global__ __launch_bounds__(512) void fwd_bf16_kernel(FwdParams p) {
     for (int s = 0; s < C::KS; ++s)
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt) {
-        const u32x4 a = *reinterpret_cast<const u32x4*>(kb + 32 * kt * C::KP + 16 * s);
+        u32x4 a;
+        if constexpr (ASYNC) a = at.row(Ks, 32 * kt, s);
+        else a = *reinterpret_cast<const u32x4*>(kb + 32 * kt * C::KP + 16 * s);
         sc[kt] = mfma32<QF16>(a, qreg[s], sc[kt]);
       }
   };
@@ -207,10 +239,15 @@ __global__ __launch_bounds__(512) void fwd_bf16_kernel(FwdParams p) {
       for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
         for (int mt = 0; mt < C::MT; ++mt) {
-          const uint16_t* base = vb + (32 * kt + 16 * hf) * C::VP + 32 * mt;
-          const u32x2 lo = lds_read_tr16(base);
-          const u32x2 hi = lds_read_tr16(base + 8 * C::VP);
-          const u32x4 a = {lo[0], lo[1], hi[0], hi[1]};
+          u32x4 a;
+          if constexpr (ASYNC) {
+            a = at.tr(Vs, 32 * kt + 16 * hf, mt);
+          } else {
+            const uint16_t* base = vb + (32 * kt + 16 * hf) * C::VP + 32 * mt;
+            const u32x2 lo = lds_read_tr16(base);
+            const u32x2 hi = lds_read_tr16(base + 8 * C::VP);
+            a = u32x4{lo[0], lo[1], hi[0], hi[1]};
+          }
           acc[mt] = mfma32<RELU>(a, pop[kt][hf], acc[mt]);
         }
   };
@@ -333,8 +370,8 @@ __global__ __launch_bounds__(512) void fwd_bf16_kernel(FwdParams p) {
     // barrier, so their latency overlaps the compute.
     const int ksplit = 4 / HP;
     constexpr int NR = 2;
-    TileRegs<D, KROPE> RS[NR];
-    auto load_tile = [&](TileRegs<D, KROPE>& X, int pos) {
+    TileRegs<D, KROPE, NW> RS[NR];
+    auto load_tile = [&](TileRegs<D, KROPE, NW>& X, int pos) {
       tile_load<D, KROPE>(X, K, V, p.table, tile_at(pos) * C::BN, S, tid);
     };
 #pragma unroll
@@ -399,6 +436,47 @@ __global__ __launch_bounds__(512) void fwd_bf16_kernel(FwdParams p) {
         }
         m_run = m_tot;
       }
+    }
+  } else if constexpr (ASYNC) {
+    // The pipeline described below, with the tiles copied to LDS: iteration t
+    // issues the copies of K'_{t+2} and V_{t+1} (into the stage halves that the
+    // last barrier freed) and waits for them at its end.  Stages are known at
+    // compile time (two iterations per trip), so every read's address is a lane
+    // offset and an immediate.
+    f32x16 sa[2], sb[2];
+    __syncthreads();
+    scores(sa, akst(0));
+    prepare(sa, 0);
+    raise();
+    __syncthreads();
+    int t = 0;
+    auto iteration = [&](f32x16 (&cur)[2], f32x16 (&nxt)[2], auto parity) {
+      constexpr int P = decltype(parity)::value;   // t & 1
+      at.load(K, tile_at(min(t + 2, ntl - 1)) * C::BN, S, akst(P));
+      at.load(V, tile_at(min(t + 1, ntl - 1)) * C::BN, S, avst(1 - P));
+      probs(cur, pop);
+      scores(nxt, akst(1 - P));
+      pin_values(pop, l_run);
+      prepare(nxt, t + 1);
+      pv(pop, avst(P));
+      raise();
+      async_wait();
+      __syncthreads();
+      ++t;
+    };
+    using P0 = std::integral_constant<int, 0>;
+    using P1 = std::integral_constant<int, 1>;
+    while (t + 2 < ntl) {
+      iteration(sa, sb, P0{});
+      iteration(sb, sa, P1{});
+    }
+    if (t + 1 < ntl) {
+      iteration(sa, sb, P0{});
+      probs(sb, pop);
+      pv(pop, avst(1));
+    } else {
+      probs(sa, pop);
+      pv(pop, avst(0));
     }
   } else {
     // Software pipeline, one barrier per tile.  Entering iteration t the
@@ -474,7 +552,6 @@ __global__ __launch_bounds__(512) void fwd_bf16_kernel(FwdParams p) {
     }
   } else {
     const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
-    static_assert(C::NW * OUT_ROWS_ELEMS<D> <= (SPARSE ? 4 : 2) * C::STAGE, "the O rows fit the staging memory");
 #pragma unroll
     for (int mt = 0; mt < C::MT; ++mt) acc[mt] *= inv;
     __syncthreads();
@@ -486,24 +563,53 @@ __global__ __launch_bounds__(512) void fwd_bf16_kernel(FwdParams p) {
   }
 }
 
+// Waves per workgroup of a dense forward.  Four (128 rows, two or three
+// workgroups per CU that do not wait at each other's barriers) against eight
+// (256 rows share each staged tile), measured with tiles copied to LDS:
+//   D = 128: B1 H32/8 causal S 500 / 2048 / 8192: 14.5 / 47.6 / 523 us with four, 20.1 / 56.0 / 515 with eight;
+//   B4 H32/8 S8192 window 1024: 602 and 625; D = 64: B8 H16 S2048 causal 97 and 108, B4 H12 S2048 no mask 65 and 78.
+// Past about 6000 keys per row at D = 128 the second copy of every tile costs
+// more than the finer workgroups give.  Rotating in the loop doubles that work
+// too, so there four waves pay only for short rows that leave CUs without an
+// eight-wave workgroup: B4 H12 D64 S 512 / 1024 14.0 / 24.0 and 17.2 / 27.2 us,
+// H32/8 D128 S 256 / 512 15.0 / 23.4 and 18.3 / 26.0, but H16 D128 S1000 44.6 and
+// 37.9.  (Slopes and bias tensors spill in that form and stay with eight.)
+template <int D, bool ASYNC>
+bool fwd_four_waves(const FwdParams& p) {
+  if (ASYNC) return p.S < 6144;
+  const int hp = heads_per_wg(p.H / p.Hkv), rows = 256 / hp;
+  return p.S <= (D == 64 ? 1024 : 512) && (long long)((p.S + rows - 1) / rows) * p.B * (p.H / hp) < 256;
+}
+
 // One launch: a block-sparse or a dense forward.
 template <int D, int ROPE, int MASK, bool ALIBI, int EXT, bool KPRE>
 int fwd_launch_one(const FwdParams& p0, hipStream_t st) {
-  using C = TileCfg<D, ROPE>;
   FwdParams p = p0;
   const int G = p.H / p.Hkv;
+  auto launch = [&](auto kernel, int nw, int rows, int max_heads) {
+    p.heads_per_wg = heads_per_wg(G) < max_heads ? heads_per_wg(G) : max_heads;
+    const int P = rows / p.heads_per_wg;
+    const long long blocks = (long long)((p.S + P - 1) / P) * p.B * p.Hkv * (G / p.heads_per_wg);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * nw), 0, st, p);
+  };
+  constexpr bool RELU = EXT == EXT_RELU || EXT == EXT_RELU_BIAS;
+  constexpr bool ASYNC = (KPRE || ROPE == ROPE_NONE) && !RELU;
   if (EXT == EXT_NONE && p.bq_ptr) {
     // block-sparse: one 64-row query block of up to 4 heads per workgroup
     p.heads_per_wg = heads_per_wg(G) < 4 ? heads_per_wg(G) : 4;
-    const long long blocks = (long long)((p.S + C::BN - 1) / C::BN) * p.B * p.Hkv * (G / p.heads_per_wg);
-    hipLaunchKernelGGL((fwd_bf16_kernel<D, ROPE, MASK, ALIBI, true, EXT_NONE, KPRE>), dim3((unsigned)blocks),
-                       dim3(C::THREADS), 0, st, p);
+    const long long blocks = (long long)((p.S + 63) / 64) * p.B * p.Hkv * (G / p.heads_per_wg);
+    hipLaunchKernelGGL((fwd_bf16_kernel<D, ROPE, MASK, ALIBI, true, EXT_NONE, KPRE, 8>), dim3((unsigned)blocks),
+                       dim3(512), 0, st, p);
   } else {
-    p.heads_per_wg = heads_per_wg(G);
-    const int P = C::ROWS / p.heads_per_wg;
-    const long long blocks = (long long)((p.S + P - 1) / P) * p.B * p.Hkv * (G / p.heads_per_wg);
-    hipLaunchKernelGGL((fwd_bf16_kernel<D, ROPE, MASK, ALIBI, false, EXT, KPRE>), dim3((unsigned)blocks),
-                       dim3(C::THREADS), 0, st, p);
+    constexpr bool ALWAYS4 = ASYNC && (D == 64 || MASK == MASK_SLIDING_WINDOW);
+    constexpr bool EITHER = !ALWAYS4 && (ASYNC || (EXT == EXT_NONE && !ALIBI));
+    if constexpr (ALWAYS4 || EITHER) {
+      if (ALWAYS4 || fwd_four_waves<D, ASYNC>(p)) {
+        launch(fwd_bf16_kernel<D, ROPE, MASK, ALIBI, false, EXT, KPRE, 4>, 4, 128, 4);
+        return hipGetLastError() == hipSuccess ? 0 : -3;
+      }
+    }
+    if constexpr (!ALWAYS4) launch(fwd_bf16_kernel<D, ROPE, MASK, ALIBI, false, EXT, KPRE, 8>, 8, 256, 8);
   }
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }

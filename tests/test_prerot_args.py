@@ -7,8 +7,8 @@ from paper_2609_13612_amd import _lib
 FAKE = 0x10000
 
 
-def _bytes(B=1, H=32, Hkv=8, S=8192, D=128, dtype=0, rope=1, mask=1, window=0, blocks=0):
-    return _lib.load().af_fwd_workspace_bytes(B, H, Hkv, S, D, dtype, rope, mask, window, blocks)
+def _bytes(B=1, H=32, Hkv=8, S=8192, D=128, dtype=0, rope=1, mask=1, window=0, norm=0, blocks=0):
+    return _lib.load().af_fwd_workspace_bytes(B, H, Hkv, S, D, dtype, rope, mask, window, norm, blocks)
 
 
 def test_long_rotated_prompts_take_the_scratch():
@@ -19,8 +19,8 @@ def test_long_rotated_prompts_take_the_scratch():
 
 
 @pytest.mark.parametrize("kw", [
-    dict(rope=0), dict(dtype=1), dict(S=256), dict(S=0), dict(B=0), dict(H=6, Hkv=4), dict(D=96), dict(S=(1 << 20) + 1),
-    dict(H=12, Hkv=12, B=4, S=512, D=64), dict(mask=2, window=1)])
+    dict(rope=0), dict(dtype=1), dict(S=128), dict(S=512, norm=1), dict(S=0), dict(B=0), dict(H=6, Hkv=4), dict(D=96), dict(S=(1 << 20) + 1),
+    dict(H=12, Hkv=12, B=4, S=512, D=64)])
 def test_other_calls_do_not(kw):
     assert _bytes(**kw) == 0
 
