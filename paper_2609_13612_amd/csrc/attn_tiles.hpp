@@ -144,7 +144,7 @@ __device__ __forceinline__ void tile_commit(TileRegs<D, ROPE, NW>& R, uint16_t* 
 }
 
 // ---------------------------------------------------------------- tiles copied straight to LDS
-// A 64-row tile that needs no arithmetic on its way (rotated keys from the
+// A tile that needs no arithmetic on its way (rotated keys from the
 // workspace, V, unrotated K) goes from global memory to LDS without passing
 // through registers (global_load_lds): the waves issue the copies and the tile
 // is there after the wait and barrier that end the iteration.  That frees the
@@ -162,16 +162,16 @@ __device__ __forceinline__ void tile_commit(TileRegs<D, ROPE, NW>& R, uint16_t* 
 // so four (or two) lane offsets and immediates address every read.
 __device__ __forceinline__ void async_copy16(const void* sbase, uint32_t voff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds)
-               : "memory", "m0");
+               : "memory");   // (nothing else in these kernels uses M0)
 }
 // Every copy this wave issued has landed (the barrier after it says so for all waves).
 __device__ __forceinline__ void async_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-template <int D, int NW>
+template <int D, int NW, int ROWS = 64>
 struct AsyncTile {
   static constexpr int GROUP = 512 + 8;        // elements of a 1 KB group and its padding
   static constexpr int RPG = 512 / D;          // rows per group
-  static constexpr int GROUPS = 64 / RPG;
+  static constexpr int GROUPS = ROWS / RPG;
   static constexpr int ELEMS = GROUPS * GROUP;
   static constexpr int NI = GROUPS / NW;       // groups each wave copies
   static_assert(GROUPS % NW == 0, "every wave copies the same number of groups");
@@ -200,7 +200,15 @@ struct AsyncTile {
 #pragma unroll
     for (int j = 0; j < NV; ++j) vb[j] = at(tr, 4 * j + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) + 4 * (lane & 1);
   }
-  // Copy rows n0 .. n0 + 63 of X (rows past S: row S - 1; n0 < S) to the stage dst.
+  // Move the reads' lane offsets by d elements (to the other stage and back),
+  // where the stage is not known at compile time.
+  __device__ __forceinline__ void flip(int d) {
+#pragma unroll
+    for (int j = 0; j < NK; ++j) kb[j] += d;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) vb[j] += d;
+  }
+  // Copy rows n0 .. n0 + ROWS - 1 of X (rows past S: row S - 1; n0 < S) to the stage dst.
   __device__ __forceinline__ void load(const uint16_t* __restrict__ X, int n0, int S, uint16_t* dst) const {
     const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)dst;
     const uint16_t* base = X + (size_t)n0 * D;

@@ -184,7 +184,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(BwdParams p, int q_blocks
 
 // Convert a staged K tile's registers from bf16 to fp16 (exact for |k| < 65504).
 template <int D>
-__device__ __forceinline__ void k_to_f16(TileRegs<D, ROPE_NONE>& R) {
+__device__ __forceinline__ void k_to_f16(TileRegs<D, ROPE_NONE, 8>& R) {
   using C = TileCfg<D, ROPE_NONE>;
 #pragma unroll
   for (int i = 0; i < C::KPT; ++i)
@@ -226,22 +226,36 @@ __device__ __forceinline__ void dq_tile_commit(const TileRegs<D, ROPE_NONE>& R, 
   }
 }
 
-// Same decomposition as the forward: 8 waves, GQA heads packed, double-buffered
-// K'/V tiles (loaded as attn_tiles.hpp does, stored in the layout above);
-// dQ'^T += K'^T dS^T with K'^T from transpose reads.
+// Same decomposition as the forward: GQA heads packed, double-buffered K'/V
+// tiles; dQ'^T += K'^T dS^T with K'^T from transpose reads.  With RoPE the
+// tiles (K' rotated, fp16, from the workspace; V) are copied straight to LDS
+// by four waves, so that two workgroups share a CU and do not wait at each
+// other's barriers; without it K is converted to fp16 as it is staged, eight
+// waves sharing that work (layout above).  What bounds the pass is the chain
+// S, dP -> softmax -> dQ of each tile, which the other waves of the SIMD hide.
+// Against eight waves staging through registers: B1 H32/8 S8192 D128 causal
+// 820 -> 788 us, window 1024 at B4 954 -> 854, B8 H16 S2048 D64 151 -> 139,
+// B3 H16/4 S1777 D128 no mask 170 -> 138.
+constexpr int dq_waves(int rope, bool sparse) { return (rope != ROPE_NONE && !sparse) ? 4 : 8; }
+
 template <int D, int ROPE, int MASK, bool ALIBI, bool SPARSE, int EXT = EXT_NONE>
-__global__ __launch_bounds__(512) void bwd_dq_kernel(BwdParams p) {
-  using C = TileCfg<D, ROPE_NONE>;            // K' arrives rotated, or K is converted to fp16 at staging
+__global__ __launch_bounds__(64 * dq_waves(ROPE, SPARSE)) __attribute__((amdgpu_waves_per_eu(2)))
+void bwd_dq_kernel(BwdParams p) {
+  constexpr bool ASYNC = ROPE != ROPE_NONE && !SPARSE;
+  using C = TileCfg<D, ROPE_NONE, dq_waves(ROPE, SPARSE)>;   // K' arrives rotated, or K is converted to fp16 at staging
+  using AT = AsyncTile<D, C::NW>;
   using L = DqTileCfg<D>;
   constexpr bool ROT = ROPE != ROPE_NONE;    // Q' and K' come rotated (fp16) from the workspace
   constexpr bool TBIAS = EXT == EXT_BIAS || EXT == EXT_RELU_BIAS;
   constexpr bool RELU = EXT == EXT_RELU || EXT == EXT_RELU_BIAS;
   static_assert(TILE_LIST_SCRATCH_BYTES <= 2 * L::STAGE * (int)sizeof(uint16_t), "the tile-list scratch fits the stages");
   // the two key-tile stages, and at the end each wave's dQ rows on their way out
-  constexpr int SMEM = (2 * L::STAGE > C::NW * OUT_ROWS_ELEMS<D>) ? 2 * L::STAGE : C::NW * OUT_ROWS_ELEMS<D>;
+  constexpr int STAGES = ASYNC ? 4 * AT::ELEMS : 2 * L::STAGE;
+  constexpr int SMEM = (STAGES > C::NW * OUT_ROWS_ELEMS<D>) ? STAGES : C::NW * OUT_ROWS_ELEMS<D>;
   __shared__ __attribute__((aligned(16))) uint16_t smem[SMEM];
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lq = lane & 31, lg = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, lg = lane >> 5;
+  const int wave = ASYNC ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const int S = p.S;
   const int HP = p.heads_per_wg;
   const int WPH = C::NW / HP;
@@ -269,6 +283,19 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdParams p) {
   const uint16_t* Kg = static_cast<const uint16_t*>(ROT ? p.kr16 : p.k) + (size_t)bg * S * D;
   const uint16_t* Vg = static_cast<const uint16_t*>(p.v) + (size_t)bg * S * D;
 
+  const int W = p.window;
+  const int ntiles = (S + C::BN - 1) / C::BN;
+  int t_begin = 0, t_end = ntiles;
+  if constexpr (MASK != MASK_NONE) t_end = min(ntiles, (p_end - 1) / C::BN + 1);
+  if constexpr (MASK == MASK_SLIDING_WINDOW) t_begin = max(0, p0 - W + 1) / C::BN;
+  // the first tile copied to LDS is in flight while the rows are loaded
+  AT at(lane, wave);
+  auto stage = [&](int t) { return smem + (t & 1) * 2 * AT::ELEMS; };   // K', then V
+  if constexpr (ASYNC) {
+    at.load(Kg, t_begin * C::BN, S, stage(0));
+    at.load(Vg, t_begin * C::BN, S, stage(0) + AT::ELEMS);
+  }
+
   u32x4 qreg[C::KS], oreg[C::KS];
   const int mc = min(m, S - 1);   // rows past S compute on row S-1 and are never stored
   load_row_operand<D, ROPE_NONE, !ROT>(qreg, Qh, nullptr, mc, S, lg);
@@ -287,12 +314,6 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdParams p) {
 
   const float c2 = p.scale * kLog2e;
   const float slope2 = ALIBI ? p.slopes[h] * kLog2e : 0.f;
-  const int W = p.window;
-  const int ntiles = (S + C::BN - 1) / C::BN;
-  int t_begin = 0, t_end = ntiles;
-  if constexpr (MASK != MASK_NONE) t_end = min(ntiles, (p_end - 1) / C::BN + 1);
-  if constexpr (MASK == MASK_SLIDING_WINDOW) t_begin = max(0, p0 - W + 1) / C::BN;
-
   // Key tiles by position i: t_begin + i, or under a block-sparse mask the
   // union of the workgroup's query blocks' active key blocks (as the forward).
   __shared__ std::conditional_t<SPARSE, TileList<true>, int> tl;
@@ -310,8 +331,10 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdParams p) {
   };
 
   const SwzLane<D> zl(lane);
-  TileRegs<D, ROPE_NONE> R;
-  if (ntl > 0) {
+  TileRegs<D, ROPE_NONE, C::NW> R;
+  if constexpr (ASYNC) {
+    async_wait();
+  } else if (ntl > 0) {
     tile_load<D, ROPE_NONE>(R, Kg, Vg, nullptr, tile_at(0) * C::BN, S, tid);
     if constexpr (!ROT) k_to_f16(R);
     dq_tile_commit<D>(R, smem, smem + L::K_ELEMS, tid);
@@ -321,10 +344,17 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdParams p) {
   for (int t = 0; t < ntl; ++t) {
     const int n0 = tile_at(t) * C::BN;
     const SwzLane<D> z = zl.opaque();
-    const uint16_t* Ks = smem + (t & 1) * L::STAGE;
-    const uint16_t* Vs = Ks + L::K_ELEMS;
+    // (the lane offsets of AsyncTile carry the stage)
+    const uint16_t* Ks = ASYNC ? smem : smem + (t & 1) * L::STAGE;
+    const uint16_t* Vs = ASYNC ? smem + AT::ELEMS : Ks + L::K_ELEMS;
     const bool more = t + 1 < ntl;
-    if (more) tile_load<D, ROPE_NONE>(R, Kg, Vg, nullptr, tile_at(t + 1) * C::BN, S, tid);
+    if constexpr (ASYNC) {
+      const int next = tile_at(min(t + 1, ntl - 1)) * C::BN;   // past the last tile: into a stage nobody reads any more
+      at.load(Kg, next, S, stage(t + 1));
+      at.load(Vg, next, S, stage(t + 1) + AT::ELEMS);
+    } else if (more) {
+      tile_load<D, ROPE_NONE>(R, Kg, Vg, nullptr, tile_at(t + 1) * C::BN, S, tid);
+    }
 
     bool visible = mw < S;
     if constexpr (SPARSE) visible = visible && ((tl.rows[t] >> jw) & 1);
@@ -339,8 +369,14 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdParams p) {
         f32x16 sc = f32x16{}, dp = f32x16{};
 #pragma unroll
         for (int k = 0; k < C::KS; ++k) {
-          const u32x4 ak = row_operand_swz<D>(Ks, z, 32 * kt, k);
-          const u32x4 av = *reinterpret_cast<const u32x4*>(Vs + (32 * kt + lq) * L::VP + 16 * k + 8 * lg);
+          u32x4 ak, av;
+          if constexpr (ASYNC) {
+            ak = at.row(Ks, 32 * kt, k);
+            av = at.row(Vs, 32 * kt, k);
+          } else {
+            ak = row_operand_swz<D>(Ks, z, 32 * kt, k);
+            av = *reinterpret_cast<const u32x4*>(Vs + (32 * kt + lq) * L::VP + 16 * k + 8 * lg);
+          }
           sc = mfma32<true>(ak, qreg[k], sc);
           dp = mfma32(av, oreg[k], dp);
         }
@@ -394,11 +430,18 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdParams p) {
 #pragma unroll
         for (int mt = 0; mt < C::MT; ++mt)
 #pragma unroll
-          for (int hf = 0; hf < 2; ++hf)
-            dq[mt] = mfma32<true>(tr_operand_swz<D>(Ks, z, 32 * kt + 16 * hf, mt), db[hf], dq[mt]);
+          for (int hf = 0; hf < 2; ++hf) {
+            u32x4 a;
+            if constexpr (ASYNC) a = at.tr(Ks, 32 * kt + 16 * hf, mt);
+            else a = tr_operand_swz<D>(Ks, z, 32 * kt + 16 * hf, mt);
+            dq[mt] = mfma32<true>(a, db[hf], dq[mt]);
+          }
       }
     }
-    if (more) {
+    if constexpr (ASYNC) {
+      async_wait();
+      at.flip((t & 1) ? -2 * AT::ELEMS : 2 * AT::ELEMS);
+    } else if (more) {
       uint16_t* Kn = smem + ((t + 1) & 1) * L::STAGE;
       if constexpr (!ROT) k_to_f16(R);
       dq_tile_commit<D>(R, Kn, Kn + L::K_ELEMS, tid);
@@ -438,17 +481,17 @@ struct BwdPasses {
     hipLaunchKernelGGL(bwd_dscale_kernel, dim3(groups), dim3(256), 0, st, p);
     hipLaunchKernelGGL((bwd_prep_kernel<D, ROPE>), dim3((unsigned)(q_blocks + k_blocks)), dim3(256), 0, st, p,
                        q_blocks);
-    using TC = TileCfg<D, ROPE_NONE>;
+    const int nw = (EXT == EXT_NONE && p.bq_ptr) ? dq_waves(ROPE, true) : dq_waves(ROPE, false);
     BwdParams pq = p;
-    pq.heads_per_wg = heads_per_wg(p.H / p.Hkv);
-    const int P = TC::ROWS / pq.heads_per_wg;
+    pq.heads_per_wg = heads_per_wg(p.H / p.Hkv) < nw ? heads_per_wg(p.H / p.Hkv) : nw;
+    const int P = 32 * nw / pq.heads_per_wg;
     const long long qblocks = (long long)((p.S + P - 1) / P) * p.B * p.Hkv * ((p.H / p.Hkv) / pq.heads_per_wg);
     if (EXT == EXT_NONE && p.bq_ptr)
-      hipLaunchKernelGGL((bwd_dq_kernel<D, ROPE, MASK, ALIBI, true>), dim3((unsigned)qblocks), dim3(TC::THREADS), 0,
+      hipLaunchKernelGGL((bwd_dq_kernel<D, ROPE, MASK, ALIBI, true>), dim3((unsigned)qblocks), dim3(64 * nw), 0,
                          st, pq);
     else
       hipLaunchKernelGGL((bwd_dq_kernel<D, ROPE, MASK, ALIBI, false, EXT>), dim3((unsigned)qblocks),
-                         dim3(TC::THREADS), 0, st, pq);
+                         dim3(64 * nw), 0, st, pq);
     if (hipGetLastError() != hipSuccess) return -3;
     // after the dQ pass, which replaced delta by sum_j P_ij dP_ij
     return launch_bwd_dkdv_bf16(D, ROPE, MASK, ALIBI, EXT, p, st);

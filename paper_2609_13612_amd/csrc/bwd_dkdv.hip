@@ -36,6 +36,26 @@ struct QTileRegs {
   float lse2, del;
 };
 
+// The tile's row statistics, one row per thread (of the first BQ).
+template <int D, int BQ>
+__device__ __forceinline__ void qstat_load(QTileRegs<D, BQ>& R, const float* __restrict__ lse2,
+                                           const float* __restrict__ delta, int m0, int S, int tid) {
+  const int ms = min(m0 + (tid & (BQ - 1)), S - 1);
+  const bool in = m0 + (tid & (BQ - 1)) < S;
+  const float l = lse2[ms], dl = delta[ms];
+  R.lse2 = in ? l : INFINITY;
+  R.del = in ? dl : 0.f;
+}
+
+template <int D, int BQ>
+__device__ __forceinline__ void qstat_commit(const QTileRegs<D, BQ>& R, float* __restrict__ lse2s,
+                                             float* __restrict__ dels, int tid) {
+  if (tid < BQ) {
+    lse2s[tid] = R.lse2;
+    dels[tid] = R.del;
+  }
+}
+
 // Rows past S are clamped to row S-1 so every load is unconditional; they get
 // LSE = +inf (so P = 0) and delta = 0, so they contribute nothing.
 template <int D, int BQ>
@@ -51,11 +71,7 @@ __device__ __forceinline__ void qtile_load(QTileRegs<D, BQ>& R, const uint16_t* 
     R.q[i] = ld16(Q + (size_t)m * D + 8 * c);
     R.o[i] = ld16(dO + (size_t)m * D + 8 * c);
   }
-  const int ms = min(m0 + (tid & (C::BQ - 1)), S - 1);
-  const bool in = m0 + (tid & (C::BQ - 1)) < S;
-  const float l = lse2[ms], dl = delta[ms];
-  R.lse2 = in ? l : INFINITY;
-  R.del = in ? dl : 0.f;
+  qstat_load<D>(R, lse2, delta, m0, S, tid);
 }
 
 // TO_F16: Q arrives as bf16 (no RoPE) and is converted as it is staged.
@@ -77,10 +93,7 @@ __device__ __forceinline__ void qtile_commit(const QTileRegs<D, BQ>& R, uint16_t
     *reinterpret_cast<u32x4*>(Qs + swz_at<D>(r, 8 * c)) = q;
     *reinterpret_cast<u32x4*>(Os + swz_at<D>(r, 8 * c)) = R.o[i];
   }
-  if (tid < C::BQ) {
-    lse2s[tid] = R.lse2;
-    dels[tid] = R.del;
-  }
+  qstat_commit<D>(R, lse2s, dels, tid);
 }
 
 // One workgroup = 8 waves = 128 keys of one (batch, K/V head).  Waves w and
@@ -90,7 +103,11 @@ __device__ __forceinline__ void qtile_commit(const QTileRegs<D, BQ>& R, uint16_t
 // latencies; their partial dK/dV are summed through LDS at the end.
 // The block's K' rows (B operand of S = Q' K'^T) and V rows (fp16, B operand
 // of dP = dO V^T) stay resident in LDS, leaving the registers to the dK/dV
-// accumulators.
+// accumulators.  Copying the query tiles straight to LDS frees 14 registers
+// and the LDS writes; the pass is bound by its operand reads and the barrier
+// that keeps its waves in step, so it gains 2 % where every CU has a workgroup
+// (B1 H32/8 S8192 D128 causal 1159 -> 1136 us) and 12 % where some have none
+// (B3 H16/4 S1777, 168 workgroups: 251 -> 221).
 template <int D, int ROPE, int MASK, bool ALIBI, bool SPARSE, int EXT = EXT_NONE>
 __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdParams p) {
   // at D = 64 a 128-row query tile halves the steps (barriers, staging) per
@@ -100,14 +117,20 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdParams p) {
   constexpr bool TBIAS = EXT == EXT_BIAS || EXT == EXT_RELU_BIAS;
   constexpr bool RELU = EXT == EXT_RELU || EXT == EXT_RELU_BIAS;
   constexpr bool ROT = ROPE != ROPE_NONE;    // Q' and K' come rotated (fp16) from the workspace
-  constexpr int SMEM = 2 * C::STAGE + 2 * C::V_ELEMS;
+  // With RoPE the query tiles (Q' and dO, fp16, from the workspace) are copied
+  // straight to LDS; without it Q is converted as it is staged.
+  constexpr bool ASYNC = ROT && !SPARSE;
+  using AT = AsyncTile<D, C::NW, C::BQ>;
+  constexpr int STAGES = ASYNC ? 4 * AT::ELEMS : 2 * C::STAGE;
+  constexpr int SMEM = STAGES + 2 * C::V_ELEMS;
   static_assert(SMEM * 2 >= 4 * 16 * C::MT * 64 * 4, "the partial-sum exchange reuses the staging memory");
   __shared__ __attribute__((aligned(16))) uint16_t smem[SMEM];
   __shared__ __attribute__((aligned(16))) float stat[2][2][C::BQ];   // [stage][lse2, delta][query]
-  uint16_t* Ks = smem + 2 * C::STAGE;
+  uint16_t* Ks = smem + STAGES;
   uint16_t* Vs = Ks + C::V_ELEMS;
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lq = lane & 31, lg = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, lg = lane >> 5;
+  const int wave = ASYNC ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const int kw = wave & 3, qh = wave >> 2;    // key block within the workgroup, query half
   const int S = p.S;
   const int BG = p.B * p.Hkv;
@@ -177,7 +200,24 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdParams p) {
   };
 
   QTileRegs<D, C::BQ> R;
-  if (steps > 0) {
+  AT at(lane, wave);
+  auto stage = [&](int s) { return smem + (s & 1) * 2 * AT::ELEMS; };   // Q', then dO
+  // Start a step's query tile on its way: the copies to LDS, and this thread's
+  // row statistics into registers.
+  auto tile_copy = [&](int s) {
+    const uint16_t *Qh, *dOh;
+    const float *l2, *dl;
+    src(s, Qh, dOh, l2, dl);
+    const int m0 = tile_of(s) * C::BQ;
+    at.load(Qh, m0, S, stage(s));
+    at.load(dOh, m0, S, stage(s) + AT::ELEMS);
+    qstat_load<D>(R, l2, dl, m0, S, tid);
+  };
+  if (ASYNC && steps > 0) {
+    tile_copy(0);
+    qstat_commit<D>(R, stat[0][0], stat[0][1], tid);
+    async_wait();
+  } else if (steps > 0) {
     const uint16_t *Qh, *dOh;
     const float *l2, *dl;
     src(0, Qh, dOh, l2, dl);
@@ -190,12 +230,23 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdParams p) {
   for (int s = 0; s < steps; ++s) {
     const int st = s & 1;
     const SwzLane<D> z = zl.opaque();
-    const uint16_t* Qs = smem + st * C::STAGE;
-    const uint16_t* Os = Qs + C::Q_ELEMS;
+    // (the lane offsets of AsyncTile carry the stage)
+    const uint16_t* Qs = ASYNC ? smem : smem + st * C::STAGE;
+    const uint16_t* Os = ASYNC ? smem + AT::ELEMS : Qs + C::Q_ELEMS;
+    auto row_op = [&](const uint16_t* tile, int r0, int k) -> u32x4 {
+      if constexpr (ASYNC) return at.row(tile, r0, k);
+      else return row_operand_swz<D>(tile, z, r0, k);
+    };
+    auto tr_op = [&](const uint16_t* tile, int r0, int mt) -> u32x4 {
+      if constexpr (ASYNC) return at.tr(tile, r0, mt);
+      else return tr_operand_swz<D>(tile, z, r0, mt);
+    };
     const float* lse2s = stat[st][0];
     const float* dels = stat[st][1];
     const bool more = s + 1 < steps;
-    if (more) {
+    if (ASYNC && more) {
+      tile_copy(s + 1);
+    } else if (more) {
       const uint16_t *Qh, *dOh;
       const float *l2, *dl;
       src(s + 1, Qh, dOh, l2, dl);
@@ -224,8 +275,8 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdParams p) {
         f32x16 sc = f32x16{}, dp = f32x16{};
   #pragma unroll
         for (int k = 0; k < C::KS; ++k) {
-          const u32x4 aq = row_operand_swz<D>(Qs, z, 32 * qt, k);
-          const u32x4 ao = row_operand_swz<D>(Os, z, 32 * qt, k);
+          const u32x4 aq = row_op(Qs, 32 * qt, k);
+          const u32x4 ao = row_op(Os, 32 * qt, k);
           const u32x4 bk = *reinterpret_cast<const u32x4*>(Ks + (32 * kw + lq) * C::VP + 16 * k + 8 * lg);
           const u32x4 bv = *reinterpret_cast<const u32x4*>(Vs + (32 * kw + lq) * C::VP + 16 * k + 8 * lg);
           sc = mfma32<true>(aq, bk, sc);
@@ -301,15 +352,15 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdParams p) {
         // each MFMA waits on a read issued one pair earlier rather than on its own.
         {
           constexpr int NI = 2 * C::MT;   // (hf, mt) pairs
-          u32x4 to = tr_operand_swz<D>(Os, z, 32 * qt, 0), tq = tr_operand_swz<D>(Qs, z, 32 * qt, 0);
+          u32x4 to = tr_op(Os, 32 * qt, 0), tq = tr_op(Qs, 32 * qt, 0);
   #pragma unroll
           for (int i = 0; i < NI; ++i) {
             const int hf = i / C::MT, mt = i % C::MT;
             const u32x4 ao = to, aq = tq;
             if (i + 1 < NI) {
               const int row = 32 * qt + 16 * ((i + 1) / C::MT), mn = (i + 1) % C::MT;
-              to = tr_operand_swz<D>(Os, z, row, mn);
-              tq = tr_operand_swz<D>(Qs, z, row, mn);
+              to = tr_op(Os, row, mn);
+              tq = tr_op(Qs, row, mn);
             }
             dv[mt] = mfma32<true>(ao, pb[hf], dv[mt]);
             dk[mt] = mfma32<true>(aq, db[hf], dk[mt]);
@@ -318,7 +369,11 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdParams p) {
       }
     }
 
-    if (more) {
+    if constexpr (ASYNC) {
+      if (more) qstat_commit<D>(R, stat[(s + 1) & 1][0], stat[(s + 1) & 1][1], tid);
+      async_wait();
+      at.flip((s & 1) ? -2 * AT::ELEMS : 2 * AT::ELEMS);
+    } else if (more) {
       const int sn = (s + 1) & 1;
       qtile_commit<D, !ROT>(R, smem + sn * C::STAGE, smem + sn * C::STAGE + C::Q_ELEMS, stat[sn][0], stat[sn][1], tid);
     }
