@@ -143,12 +143,13 @@ int attnfuse_fwd(const void* Q, const void* K, const void* V, void* O, float* LS
 size_t attnfuse_bwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int rope);
 
 /*
- * Backward of attnfuse_fwd (Section 4.4: no atomics -- a preprocessing pass,
- * a dQ pass over key tiles and a dK/dV pass over query tiles; probabilities
- * are re-derived from the saved LSE).  The preprocessing pass computes the
- * row statistics and, with RoPE, rotates Q and K once into the workspace (both
- * later passes read every tile many times, so rotating once is cheaper than
- * re-rotating per visit); the gradients leave through the inverse rotation:
+ * Backward of attnfuse_fwd (Section 4.4: no atomics -- a pass over dO and K
+ * that finds the gradient's scale and rotates K, a dQ pass over key tiles and a
+ * dK/dV pass over query tiles; probabilities are re-derived from the saved
+ * LSE).  The dQ pass also forms the row statistics and leaves the rotated Q in
+ * the workspace (the tiles of both passes are read many times, so rotating once
+ * is cheaper than re-rotating per visit); the gradients leave through the
+ * inverse rotation:
  * dQ = R^T dQ', dK = R^T dK'.  For grouped-query attention dK and dV sum over
  * the H/H_kv query heads of their group.
  *

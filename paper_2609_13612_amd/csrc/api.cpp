@@ -74,7 +74,7 @@ bool supported_d(int D) { return D == 64 || D == 128; }
 // Backward workspace: [delta f32 | lse2 f32 | dO fp16 | dO scale f32 | partial
 // max |dO| u32 | Q' fp16 | K' fp16], each section starting on a 256-byte
 // boundary; the last two only with RoPE.  The partial maxima cover chunks of
-// kDmaxChunk elements of each (batch, K/V head)'s dO.
+// at least kDmaxChunk elements of each (batch, K/V head)'s dO.
 constexpr long long kDmaxChunk = 16384;
 
 struct BwdWorkspace {
@@ -235,7 +235,7 @@ int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const v
   p.do16 = wb + ws.do16;
   p.dscale = reinterpret_cast<float*>(wb + ws.dscale);
   p.dmax = reinterpret_cast<uint32_t*>(wb + ws.dmax);
-  p.dmax_chunks = ws.dmax_chunks;
+  p.dmax_chunks = ws.dmax_chunks < af::DMAX_PARTS ? ws.dmax_chunks : af::DMAX_PARTS;
   p.qr16 = (rope != AF_ROPE_NONE) ? wb + ws.qr16 : nullptr;
   p.kr16 = (rope != AF_ROPE_NONE) ? wb + ws.kr16 : nullptr;
   p.B = B; p.H = H; p.Hkv = H_kv; p.S = S;

@@ -3,20 +3,20 @@
 //
 // The passes of Section 4.4, no atomics: every output tile has exactly one
 // writer.
-//   0. bwd_dmax, bwd_dscale: sigma, the power of two per (batch, K/V head)
-//                 that brings the group's largest |dO| into [1, 2).
-//   1. bwd_prep:  delta_i = rowsum(dO_i * O_i), LSE_i in log2 units, sigma dO
-//                 in fp16, and with RoPE Q' = R Q and K' = R K rotated once
-//                 into the workspace (fp16).  The later kernels read each Q'
-//                 and K' tile many times (dK/dV reads every Q' tile once per
-//                 key block), so one rotation pass replaces all of those.
-//   2. bwd_dq:    one workgroup per 256 query rows (GQA heads packed, as in
-//                 the forward); it loops over visible key tiles:
-//                 dQ' += scale dS K',  dQ = R^T dQ'.  Since it forms P and dP
-//                 for every visible key of its rows, it also sums the
-//                 softmax backward's row term delta_i = sum_j P_ij dP_ij in
-//                 fp32 (with P renormalised by its own row sum) and writes it,
-//                 and the renormalised LSE, over the preprocessing pass's.
+//   1. bwd_pre:   partial maxima of |dO| per (batch, K/V head), and with RoPE
+//                 K' = R K rotated once into the workspace (fp16): the later
+//                 kernels read every K' tile many times.
+//   2. bwd_dq:    one workgroup per 128 or 256 query rows (GQA heads packed, as
+//                 in the forward); it loops over visible key tiles:
+//                 dQ' += scale dS K',  dQ = R^T dQ'.  Before the loop it forms
+//                 what else the passes need of its rows from the registers that
+//                 hold them: sigma (the power of two that brings the group's
+//                 largest |dO| into [1, 2)), delta_i = rowsum(dO_i * O_i), and
+//                 for the dK/dV pass Q' = R Q and sigma dO in fp16 in the
+//                 workspace.  Since it forms P and dP for every visible key of
+//                 its rows, it also sums the softmax backward's row term
+//                 delta_i = sum_j P_ij dP_ij in fp32 (with P renormalised by
+//                 its own row sum) and leaves it, and the renormalised LSE.
 //   3. bwd_dkdv:  (bwd_dkdv.hip) one workgroup per 128 keys of one (batch,
 //                 K/V head); it loops over the query heads of the GQA group
 //                 and their visible query tiles, re-deriving P = exp(S - LSE)
@@ -25,7 +25,7 @@
 // delta from rowsum(dO o O) equals sum_j P_ij dP_ij only for the exact O;
 // the bf16 O a forward stores moves it by O's rounding, which reaches dK and
 // dQ through P_ij (dP_ij - delta_i).  The dK/dV pass therefore runs last, on
-// the dQ pass's sum; the dQ pass itself uses the preprocessing pass's value.
+// the dQ pass's sum; the dQ pass itself uses rowsum(dO o O).
 //
 // Scaling: the fp16 MFMA operands dO and dS carry the factor sigma, so their
 // magnitudes sit near 1 whatever the gradient's scale (unscaled bf16
@@ -55,115 +55,57 @@
 
 namespace af {
 
-// ---------------------------------------------------------------- dO scale
-// Partial maxima of |dO| over chunks of each (batch, K/V head)'s G query heads
-// (contiguous in [B, H, S, D]), as bf16 magnitude bits: the bit patterns of
-// non-negative bf16 values order like the values, so the maximum is an
-// integer maximum.
-constexpr int DMAX_CHUNK = 16384;   // dO elements per partial maximum
-
-template <int D>
-__global__ __launch_bounds__(256) void bwd_dmax_kernel(BwdParams p) {
-  const int nch = p.dmax_chunks;
-  const int bg = blockIdx.x / nch, c = blockIdx.x - bg * nch;
-  const long long n = (long long)(p.H / p.Hkv) * p.S * D;
-  const uint16_t* src = static_cast<const uint16_t*>(p.dout) + (long long)bg * n;
-  const long long e1 = min(n, (long long)(c + 1) * DMAX_CHUNK);
-  uint32_t mx = 0;
-  for (long long e = (long long)c * DMAX_CHUNK + 8 * threadIdx.x; e < e1; e += 8 * 256) {   // n % 8 == 0
-    const u32x4 x = ld16(src + e);
-#pragma unroll
-    for (int w = 0; w < 4; ++w) mx = max(mx, max(x[w] & 0x7fffu, (x[w] >> 16) & 0x7fffu));
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
-  __shared__ uint32_t part[4];
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0) p.dmax[blockIdx.x] = max(max(part[0], part[1]), max(part[2], part[3]));
-}
-
-// sigma = 2^(127 - E) for the largest |dO| with biased exponent E, so that
-// max |dO| * sigma lies in [1, 2); clamped to [2^-126, 2^126].  1 when the
-// group's dO is all zero or holds an inf / NaN.  One workgroup per group.
-__global__ __launch_bounds__(256) void bwd_dscale_kernel(BwdParams p) {
-  const int bg = blockIdx.x, nch = p.dmax_chunks;
-  uint32_t mx = 0;
-  for (int c = threadIdx.x; c < nch; c += 256) mx = max(mx, p.dmax[(long long)bg * nch + c]);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
-  __shared__ uint32_t part[4];
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    mx = max(max(part[0], part[1]), max(part[2], part[3]));
-    const int E = (int)(mx >> 7);   // bf16 biased exponent (the sign bit is clear)
-    float sig = 1.f;
-    if (mx != 0u && E != 255) sig = __uint_as_float((uint32_t)min(max(254 - max(E, 1), 1), 253) << 23);
-    p.dscale[bg] = sig;
-  }
-}
-
-// ---------------------------------------------------------------- preprocessing
-// One thread per (row, chunk pair c): chunks c and c + D/16 (dims 8c.. and
-// D/2 + 8c..), which are NeoX partners; interleaved pairs stay in-chunk.
-// Blocks [0, q_blocks) cover the B*H query rows, the rest the B*H_kv key rows.
+// ---------------------------------------------------------------- before the dQ pass
+// Blocks [0, B H_kv dmax_chunks): partial maxima of |dO| over chunks of each
+// (batch, K/V head)'s G query heads (contiguous in [B, H, S, D]), as bf16
+// magnitude bits: the bit patterns of non-negative bf16 values order like the
+// values, so the maximum is an integer maximum.  With RoPE the blocks after
+// them rotate the key rows, one thread per chunk pair c (dims 8c.. and
+// D/2 + 8c.., NeoX partners; interleaved pairs stay in-chunk).  One pass over
+// dO and K, bound by HBM.  The rest of a preprocessing pass (delta, sigma dO,
+// Q', sigma itself) happens in the dQ pass, which holds those rows anyway: as
+// passes of their own they moved 370 MB more at B1 H32/8 S8192 D128 and cost
+// 64 us of 2.56 ms, at B8 H16 S2048 D64 43 of 515, at B4 H12 S4096 D64
+// block-sparse 16 of 293.
 template <int D, int ROPE>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(BwdParams p, int q_blocks) {
-  constexpr int TPR = D / 16;            // threads per row
-  constexpr int RPB = 256 / TPR;         // rows per block
-  const int c = threadIdx.x % TPR;
-  const int d0 = 8 * c, d1 = D / 2 + 8 * c;
-  if ((int)blockIdx.x < q_blocks) {
-    const long long rows = (long long)p.B * p.H * p.S;
-    const long long row = (long long)blockIdx.x * RPB + threadIdx.x / TPR;
-    const long long rc = row < rows ? row : rows - 1;   // clamp: every lane joins the reduction
-    const int hq = (int)((rc / p.S) % p.H), bq = (int)(rc / ((long long)p.S * p.H));
-    const float sig = p.dscale[bq * p.Hkv + hq / (p.H / p.Hkv)];
-    const uint16_t* dOr = static_cast<const uint16_t*>(p.dout) + rc * D;
-    const uint16_t* Or = static_cast<const uint16_t*>(p.o) + rc * D;
-    const u32x4 a0 = ld16(dOr + d0), a1 = ld16(dOr + d1);
-    const u32x4 o0 = ld16(Or + d0), o1 = ld16(Or + d1);
-    float acc = 0.f;
+__global__ __launch_bounds__(256) void bwd_pre_kernel(BwdParams p, int dmax_blocks) {
+  if ((int)blockIdx.x < dmax_blocks) {
+    const int nch = p.dmax_chunks;
+    const int bg = blockIdx.x / nch, c = blockIdx.x - bg * nch;
+    const long long n = (long long)(p.H / p.Hkv) * p.S * D;
+    const long long per = ((n + nch - 1) / nch + 7) & ~7ll;   // elements per chunk (n % 8 == 0)
+    const uint16_t* src = static_cast<const uint16_t*>(p.dout) + (long long)bg * n;
+    const long long e1 = min(n, (c + 1) * per);
+    uint32_t mx = 0;
+    constexpr int U = 8, STRIDE = 8 * 256;   // loads in flight per thread
+    long long e = c * per + 8 * threadIdx.x;
+    for (; e + (U - 1) * STRIDE < e1; e += U * STRIDE) {
+      u32x4 x[U];
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
-      acc += bf_lo(a0[w]) * bf_lo(o0[w]) + bf_hi(a0[w]) * bf_hi(o0[w]) + bf_lo(a1[w]) * bf_lo(o1[w]) +
-             bf_hi(a1[w]) * bf_hi(o1[w]);
+      for (int u = 0; u < U; ++u) x[u] = ld16(src + e + u * STRIDE);
 #pragma unroll
-    for (int off = TPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, TPR);
-    if (row < rows) {
-      u32x4 h0, h1;
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        h0[w] = pack_f16(bf_lo(a0[w]) * sig, bf_hi(a0[w]) * sig);
-        h1[w] = pack_f16(bf_lo(a1[w]) * sig, bf_hi(a1[w]) * sig);
-      }
-      uint16_t* dst = static_cast<uint16_t*>(p.do16) + row * D;
-      st16(dst + d0, h0);
-      st16(dst + d1, h1);
-      if (c == 0) {
-        p.delta[row] = acc * sig;
-        const float l = p.lse ? p.lse[row] : 0.f;   // relu attention has no LSE
-        p.lse2[row] = (l == -INFINITY) ? INFINITY : l * kLog2e;
-      }
-      if constexpr (ROPE != ROPE_NONE) {
-        const int pos = (int)(row % p.S);
-        const uint16_t* Qr = static_cast<const uint16_t*>(p.q) + row * D;
-        u32x4 q0 = ld16(Qr + d0), q1 = ld16(Qr + d1);
-        if constexpr (ROPE == ROPE_NEOX) {
-          rotate_neox8<false, true>(q0, q1, p.table + (size_t)pos * (D / 2) + 8 * c);
-        } else {
-          rotate_interleaved8<false, true>(q0, p.table + (size_t)pos * (D / 2) + 4 * c);
-          rotate_interleaved8<false, true>(q1, p.table + (size_t)pos * (D / 2) + D / 4 + 4 * c);
-        }
-        uint16_t* qd = static_cast<uint16_t*>(p.qr16) + row * D;
-        st16(qd + d0, q0);
-        st16(qd + d1, q1);
-      }
+        for (int w = 0; w < 4; ++w) mx = max(mx, max(x[u][w] & 0x7fffu, (x[u][w] >> 16) & 0x7fffu));
     }
+    for (; e < e1; e += STRIDE) {
+      const u32x4 x = ld16(src + e);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) mx = max(mx, max(x[w] & 0x7fffu, (x[w] >> 16) & 0x7fffu));
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+    __shared__ uint32_t part[4];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) p.dmax[blockIdx.x] = max(max(part[0], part[1]), max(part[2], part[3]));
   } else if constexpr (ROPE != ROPE_NONE) {
+    constexpr int TPR = D / 16;            // threads per row
+    constexpr int RPB = 256 / TPR;         // rows per block
+    const int c = threadIdx.x % TPR;
+    const int d0 = 8 * c, d1 = D / 2 + 8 * c;
     const long long rows = (long long)p.B * p.Hkv * p.S;
-    const long long row = (long long)(blockIdx.x - q_blocks) * RPB + threadIdx.x / TPR;
+    const long long row = (long long)(blockIdx.x - dmax_blocks) * RPB + threadIdx.x / TPR;
     if (row < rows) {
       const int pos = (int)(row % p.S);
       const uint16_t* Kr = static_cast<const uint16_t*>(p.k) + row * D;
@@ -181,6 +123,24 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(BwdParams p, int q_blocks
   }
 }
 
+// sigma of a (batch, K/V head) from its partial maxima (one wave, every lane
+// gets it): 2^(127 - E) for the largest |dO| with biased exponent E, so that
+// max |dO| * sigma lies in [1, 2); clamped to [2^-126, 2^126].  1 when the
+// group's dO is all zero or holds an inf / NaN.
+__device__ __forceinline__ float group_scale(const BwdParams& p, int bg, int lane) {
+  static_assert(DMAX_PARTS == 4 * 64, "four partial maxima per lane");
+  uint32_t mx = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int c = lane + 64 * j;
+    if (c < p.dmax_chunks) mx = max(mx, p.dmax[(long long)bg * p.dmax_chunks + c]);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+  const int E = (int)(mx >> 7);   // bf16 biased exponent (the sign bit is clear)
+  if (mx == 0u || E == 255) return 1.f;
+  return __uint_as_float((uint32_t)min(max(254 - max(E, 1), 1), 253) << 23);
+}
 
 // Convert a staged K tile's registers from bf16 to fp16 (exact for |k| < 65504).
 template <int D>
@@ -278,7 +238,7 @@ void bwd_dq_kernel(BwdParams p) {
   const int p_end = min(p0 + P, S);
   const size_t bh = (size_t)b * p.H + h;
 
-  const uint16_t* Qh = static_cast<const uint16_t*>(ROT ? p.qr16 : p.q) + bh * S * D;
+  const uint16_t* Qh = static_cast<const uint16_t*>(p.q) + bh * S * D;
   const uint16_t* dOh = static_cast<const uint16_t*>(p.dout) + bh * S * D;
   const uint16_t* Kg = static_cast<const uint16_t*>(ROT ? p.kr16 : p.k) + (size_t)bg * S * D;
   const uint16_t* Vg = static_cast<const uint16_t*>(p.v) + (size_t)bg * S * D;
@@ -298,13 +258,44 @@ void bwd_dq_kernel(BwdParams p) {
 
   u32x4 qreg[C::KS], oreg[C::KS];
   const int mc = min(m, S - 1);   // rows past S compute on row S-1 and are never stored
-  load_row_operand<D, ROPE_NONE, !ROT>(qreg, Qh, nullptr, mc, S, lg);
-  load_row_operand<D, ROPE_NONE>(oreg, dOh, nullptr, mc, S, lg);
-  const float lse2 = (m < S) ? p.lse2[bh * S + mc] : INFINITY;
+  const float sig = group_scale(p, bg, lane);
+  if (tid == 0 && hg == 0 && p0 == 0) p.dscale[bg] = sig;   // for the dK/dV pass
+  load_row_operand<D, ROPE, !ROT>(qreg, Qh, p.table, mc, S, lg);   // Q' (fp16)
+  load_row_operand<D, ROPE_NONE>(oreg, dOh, nullptr, mc, S, lg);   // dO as it is
+  // sigma delta_i from rowsum(dO o O), and LSE_i in log2 units (+inf for an
+  // empty row, so its P is 0); relu attention has neither
+  float lse2 = INFINITY, del = 0.f;
+  if constexpr (!RELU) {
+    const uint16_t* Oh = static_cast<const uint16_t*>(p.o) + bh * S * D + (size_t)mc * D + 8 * lg;
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s) {
+      const u32x4 o = ld16(Oh + 16 * s);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) del += bf_lo(oreg[s][w]) * bf_lo(o[w]) + bf_hi(oreg[s][w]) * bf_hi(o[w]);
+    }
+    del = (m < S) ? pair_sum(del) * sig : 0.f;
+    const float l = p.lse[bh * S + mc];
+    lse2 = (m < S && l != -INFINITY) ? l * kLog2e : INFINITY;
+  }
+  // the dK/dV pass's operands of these rows: sigma dO, and Q' under RoPE
+  if (m < S) {
+    const size_t row = (bh * S + m) * D + 8 * lg;
+    uint16_t* od = static_cast<uint16_t*>(p.do16) + row;
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s) {
+      u32x4 x;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) x[w] = pack_f16(bf_lo(oreg[s][w]) * sig, bf_hi(oreg[s][w]) * sig);
+      st16(od + 16 * s, x);
+    }
+    if constexpr (ROT) {
+      uint16_t* qd = static_cast<uint16_t*>(p.qr16) + row;
+#pragma unroll
+      for (int s = 0; s < C::KS; ++s) st16(qd + 16 * s, qreg[s]);
+    }
+  }
   const float* __restrict__ brow = nullptr;       // this lane's row of the bias tensor
   if constexpr (TBIAS) brow = p.bias + b * p.bias_sb + h * p.bias_sh + mc * p.bias_sq;
-  const float del = (m < S) ? p.delta[bh * S + mc] : 0.f;   // sigma delta_i from rowsum(dO o O)
-  const float sig = p.dscale[bg];
   float dsum = 0.f;   // this lane's part of sum_j P_ij dP_ij (unscaled)
   float lsum = 0.f;   // and of sum_j P_ij
 
@@ -343,7 +334,7 @@ void bwd_dq_kernel(BwdParams p) {
 
   for (int t = 0; t < ntl; ++t) {
     const int n0 = tile_at(t) * C::BN;
-    const SwzLane<D> z = zl.opaque();
+    const SwzLane<D> z = ASYNC ? zl : zl.opaque();   // (AsyncTile has its own offsets)
     // (the lane offsets of AsyncTile carry the stage)
     const uint16_t* Ks = ASYNC ? smem : smem + (t & 1) * L::STAGE;
     const uint16_t* Vs = ASYNC ? smem + AT::ELEMS : Ks + L::K_ELEMS;
@@ -472,15 +463,10 @@ struct BwdPasses {
   template <int D, int ROPE, int MASK, bool ALIBI, int EXT>
   static int run(const BwdParams& p, hipStream_t st) {
     constexpr int RPB = 256 / (D / 16);
-    const long long qrows = (long long)p.B * p.H * p.S;
     const long long krows = (ROPE != ROPE_NONE) ? (long long)p.B * p.Hkv * p.S : 0;
-    const int q_blocks = (int)((qrows + RPB - 1) / RPB);
     const int k_blocks = (int)((krows + RPB - 1) / RPB);
-    const unsigned groups = (unsigned)(p.B * p.Hkv);
-    hipLaunchKernelGGL((bwd_dmax_kernel<D>), dim3(groups * (unsigned)p.dmax_chunks), dim3(256), 0, st, p);
-    hipLaunchKernelGGL(bwd_dscale_kernel, dim3(groups), dim3(256), 0, st, p);
-    hipLaunchKernelGGL((bwd_prep_kernel<D, ROPE>), dim3((unsigned)(q_blocks + k_blocks)), dim3(256), 0, st, p,
-                       q_blocks);
+    const int d_blocks = p.B * p.Hkv * p.dmax_chunks;
+    hipLaunchKernelGGL((bwd_pre_kernel<D, ROPE>), dim3((unsigned)(d_blocks + k_blocks)), dim3(256), 0, st, p, d_blocks);
     const int nw = (EXT == EXT_NONE && p.bq_ptr) ? dq_waves(ROPE, true) : dq_waves(ROPE, false);
     BwdParams pq = p;
     pq.heads_per_wg = heads_per_wg(p.H / p.Hkv) < nw ? heads_per_wg(p.H / p.Hkv) : nw;

@@ -10,7 +10,7 @@ namespace af {
 
 // ---------------------------------------------------------------- dK / dV
 // Query-side tile of the dK/dV kernel: BQ_ query rows of Q' (fp16, rotated by
-// the preprocessing kernel) or Q (bf16, converted to fp16 as it is staged)
+// the dQ pass) or Q (bf16, converted to fp16 as it is staged)
 // and of dO (fp16), plus their LSE (log2 units) and delta.
 template <int D, int BQ_ = 64>
 struct QTileCfg {
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdParams p) {
   const int nw = nb + 32 * kw;        // first key of this wave
   const int n = nw + lq;              // this lane's key
 
-  // K' (fp16, rotated by the preprocessing kernel) or K (bf16) as is, and V
+  // K' (fp16, rotated by the first pass) or K (bf16) as is, and V
   // converted to fp16; rows past S clamped (their results are not stored)
   const uint16_t* Kg = static_cast<const uint16_t*>(ROT ? p.kr16 : p.k) + (size_t)bg * S * D;
   const uint16_t* Vg = static_cast<const uint16_t*>(p.v) + (size_t)bg * S * D;
