@@ -1,0 +1,49 @@
+"""Decode over caches of different lengths, where the sequences are cut into
+pieces by their lengths (batches whose even chunks would be long): against the
+fp64 oracle, with lengths at the edges of tiles and pieces, empty and over-long
+ones, a window, more sequences than a wave has lanes, and workspaces of exactly
+the size the library asks for."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import announce, assert_bf16_close, assert_lse_close, f64, need_gpu
+from paper_2609_13612_amd import api, inputs
+
+pytestmark = pytest.mark.gpu
+
+MANY = [(37 * i) % 4001 for i in range(70)]
+CASES = [
+    (4, 8, 4, 18000, 128, [18000, 1, 5000, 9037], "causal", None, False, "neox"),
+    (5, 4, 4, 14000, 128, [0, 14000, -3, 20000, 31], "causal", None, True, "none"),
+    (3, 32, 8, 12000, 128, [11999, 4096, 64], "sliding_window", 3000, False, "interleaved"),
+    (2, 32, 1, 140000, 128, [70001, 139999], "causal", None, False, "neox"),
+    (70, 4, 1, 4000, 128, MANY, "causal", None, False, "neox"),
+    (4, 12, 12, 12000, 64, [12000, 700, 6001, 33], "sliding_window", 5000, True, "none"),
+]
+
+
+@pytest.mark.parametrize("B,H,Hkv,S,D,lens,mask,window,alibi,rope", CASES, ids=lambda x: str(x)[:20])
+def test_cut_by_length(B, H, Hkv, S, D, lens, mask, window, alibi, rope):
+    need_gpu()
+    announce(f"decode ragged B={B} H={H}/{Hkv} S={S} D={D} {mask} {rope}")
+    c = inputs.make_decode(B, H, Hkv, S, D, seed=S)
+    slopes = inputs.alibi_slopes(H) if alibi else None
+    dev = {n: c[n].cuda() for n in ("q", "k", "v")}
+    ln = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    n = api.attnfuse_decode_workspace_bytes(B, H, Hkv, S, D)
+    guard = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    o, lse = api.attnfuse_decode(dev["q"], dev["k"], dev["v"], ln, rope=rope, mask=mask, window=window,
+                                 alibi_slopes=None if slopes is None else slopes.cuda(), workspace=guard[:n])
+    torch.cuda.synchronize()
+    assert (guard[n:] == 0x5A).all(), "written past the workspace"
+    live = [b for b in range(B) if lens[b] >= 1]
+    O, L = np.zeros((B, H, D)), np.full((B, H), -np.inf)
+    O[live], L[live] = oracle.decode_forward(
+        f64(c["q"])[live], f64(c["k"])[live], f64(c["v"])[live], [min(lens[b], S) for b in live], rope=rope,
+        theta=10000.0, mask=mask, window=window, alibi_slopes=None if slopes is None else f64(slopes))
+    assert_bf16_close(o, O, "O")
+    got = f64(lse)
+    assert np.array_equal(np.isinf(got), np.isinf(L))
+    assert_lse_close(lse[live], L[live], "LSE")
