@@ -139,6 +139,9 @@ int attnfuse_fwd(const void* Q, const void* K, const void* V, void* O, float* LS
  * + 4*B*H_kv*ceil(H/H_kv*S*D / 16384)   partial maxima of |dO|
  * + 2*(B*H + B*H_kv)*S*D     with RoPE only: Q' = R Q and K' = R K, rotated
  *                            once and rounded to fp16
+ * + 8*n*B*H_kv*S*D         where n > 1 workgroups share a key block in the dK/dV
+ *                          pass (few K/V heads or short sequences; n <= 8):
+ *                          their fp32 partial dK and dV
  * Returns 0 for invalid sizes. */
 size_t attnfuse_bwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int rope);
 

@@ -30,8 +30,8 @@ DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", f"-I{INCLUDE}", f"-I{CSRC}",
           "-Wall", "-Wno-unused-function"]
 
-SOURCES = ["api.cpp", "rope.hip", "fwd_bf16.hip", "fwd_prerot.hip", "fwd_norope.hip", "fwd_fp32.hip", "bwd_bf16.hip", "bwd_dkdv.hip", "bwd_fp32.hip",
-           "decode.hip"]
+SOURCES = ["api.cpp", "rope.hip", "fwd_bf16.hip", "fwd_prerot.hip", "fwd_norope.hip", "fwd_fp32.hip", "bwd_bf16.hip",
+           "bwd_dkdv.hip", "bwd_dkdv_split.hip", "bwd_fp32.hip", "decode.hip"]
 # Code-generation options of single translation units.  The dK/dV kernels
 # run faster when the machine scheduler keeps its first schedule instead of
 # re-scheduling high-register-pressure regions without memory-op clustering
@@ -39,7 +39,8 @@ SOURCES = ["api.cpp", "rope.hip", "fwd_bf16.hip", "fwd_prerot.hip", "fwd_norope.
 # 1024-key window, 1.3 % at D = 64, 0.6 % with ALiBi; no instantiation
 # spills).  The dQ kernels keep the default: with the option their ALiBi and
 # window instantiations ran 5-10 % slower.
-SOURCE_FLAGS = {"bwd_dkdv.hip": ["-mllvm", "-amdgpu-disable-unclustered-high-rp-reschedule=1"]}
+_DKDV = ["-mllvm", "-amdgpu-disable-unclustered-high-rp-reschedule=1"]
+SOURCE_FLAGS = {"bwd_dkdv.hip": _DKDV, "bwd_dkdv_split.hip": _DKDV}
 
 
 def _compile(src):

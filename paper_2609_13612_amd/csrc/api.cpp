@@ -71,15 +71,51 @@ int check_attn(int mask, int window, float scale) {
 
 bool supported_d(int D) { return D == 64 || D == 128; }
 
+// Workgroups that share one key block's (query head, query tile) steps in the
+// dK/dV pass.  Few K/V heads or a short sequence leave CUs without one of its
+// 128-key workgroups while each walks every query head of its group; splitting
+// costs fp32 partials, written and read once at 4.5 TB/s, and a launch.  A step
+// takes 2.2 us (64 queries, D = 128) or 3.0 (128 queries, D = 64).  Causal key
+// blocks start longest first, so the pass ends with the longest or with the
+// chip's share of the whole; equal ones run in rounds of 256.  Whole backward
+// without / with, us: H32/8 D128 causal B1 S 256 / 512 / 1024 / 2048 / 4096 58 /
+// 95 / 167 / 340 / 782 and 44 / 56 / 91 / 202 / 582; B3 H16/4 S1777 no mask 404 and
+// 366; B2 H8/2 S4000 D64 causal 364 and 195.
+int bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window) {
+  const int G = H / H_kv, BQ = D == 64 ? 128 : 64;
+  const double nkb = (S + 127) / 128, nt = (S + BQ - 1) / BQ, units = (double)B * H_kv;
+  double longest = nt, sum = nkb * nt;   // query tiles of the longest key block, and of all
+  if (mask == AF_MASK_CAUSAL) sum = nkb * (nt + 128.0 / BQ) / 2.0;
+  if (mask == AF_MASK_SLIDING_WINDOW) {
+    longest = std::fmin(nt, (128.0 + window) / BQ + 1.0);
+    sum = nkb * longest;
+  }
+  longest *= G;
+  const double share = sum * G * units / 256.0, step = D == 64 ? 3.0 : 2.2;
+  const double part_us = units * S * D * 4.0 * 2 * 2 / 4.5e6;   // of one split: dK' and dV, out and in
+  double best = 0.0, first = 0.0;
+  int n = 1;
+  for (int k : {1, 2, 3, 4, 6, 8}) {
+    if (k > longest) break;
+    const double each = std::ceil(longest / k);
+    double us = step * (mask == AF_MASK_CAUSAL ? std::fmax(each, share) : std::ceil(nkb * units * k / 256.0) * each);
+    if (k == 1) best = first = us;
+    else if ((us += 4.0 + k * part_us) < best && us < 0.9 * first) best = us, n = k;
+  }
+  return n;
+}
+
 // Backward workspace: [delta f32 | lse2 f32 | dO fp16 | dO scale f32 | partial
-// max |dO| u32 | Q' fp16 | K' fp16], each section starting on a 256-byte
-// boundary; the last two only with RoPE.  The partial maxima cover chunks of
+// max |dO| u32 | Q' fp16 | K' fp16 | partial dK' and dV f32], each section
+// starting on a 256-byte boundary; Q' and K' only with RoPE, the partials only
+// where some mask's dK/dV pass is split.  The partial maxima cover chunks of
 // at least kDmaxChunk elements of each (batch, K/V head)'s dO.
 constexpr long long kDmaxChunk = 16384;
 
 struct BwdWorkspace {
-  size_t delta, lse2, do16, dscale, dmax, qr16, kr16, total;
+  size_t delta, lse2, do16, dscale, dmax, qr16, kr16, part, total;
   int dmax_chunks;
+  int splits;   // the partials there is room for
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -99,6 +135,15 @@ BwdWorkspace bwd_workspace(int B, int H, int H_kv, int S, int D, int rope) {
     w.qr16 = off; off += align256(rows * D * 2);
     w.kr16 = off; off += align256(krows * D * 2);
   }
+  // the size does not know the mask: room for the larger of the two that fix
+  // the split by the sizes alone (a window takes at most that)
+  w.splits = 1;
+  if (supported_d(D)) {
+    const int none = bwd_splits(B, H, H_kv, S, D, AF_MASK_NONE, 0), causal = bwd_splits(B, H, H_kv, S, D, AF_MASK_CAUSAL, 0);
+    w.splits = none > causal ? none : causal;
+  }
+  w.part = off;
+  if (w.splits > 1) off += align256((size_t)w.splits * 2 * krows * D * sizeof(float));
   w.total = off;
   return w;
 }
@@ -248,6 +293,12 @@ int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const v
   p.do16 = wb + ws.do16;
   p.dscale = reinterpret_cast<float*>(wb + ws.dscale);
   p.dmax = reinterpret_cast<uint32_t*>(wb + ws.dmax);
+  p.splits = 1;
+  if (dtype == AF_DTYPE_BF16) {   // (a block mask: as without one, whose sums it then equals where all is active)
+    const int n = bwd_splits(B, H, H_kv, S, D, mask, window < S ? window : S);
+    p.splits = n < ws.splits ? n : ws.splits;
+    p.part = reinterpret_cast<float*>(wb + ws.part);
+  }
   p.dmax_chunks = ws.dmax_chunks < af::DMAX_PARTS ? ws.dmax_chunks : af::DMAX_PARTS;
   p.qr16 = (rope != AF_ROPE_NONE) ? wb + ws.qr16 : nullptr;
   p.kr16 = (rope != AF_ROPE_NONE) ? wb + ws.kr16 : nullptr;

@@ -53,6 +53,8 @@ struct BwdParams {
   const float* slopes;
   float scale;
   const float2* table;
+  int splits;             // dK/dV: workgroups that share a key block's query tiles (1: no partials)
+  float* part;            // splits > 1: their partial dK' and dV, [splits][2][B*H_kv*S][D]
   int heads_per_wg;       // set by the launcher for the dQ kernel
   const int* bq_ptr;      // block-sparse mask by 64-row query block (CSR), or nullptr
   const int* bk_idx;
@@ -96,6 +98,8 @@ int launch_fwd_fp32(int D, int rope, int mask, bool alibi, const FwdParams& p, h
 int launch_bwd_bf16(int D, int rope, int mask, bool alibi, int ext, const BwdParams& p, hipStream_t st);
 // The dK/dV pass alone (the last launch of launch_bwd_bf16).
 int launch_bwd_dkdv_bf16(int D, int rope, int mask, bool alibi, int ext, const BwdParams& p, hipStream_t st);
+// The same with p.splits > 1 workgroups per key block, and the reduction of their partials.
+int launch_bwd_dkdv_split(int D, int rope, int mask, bool alibi, int ext, const BwdParams& p, hipStream_t st);
 int launch_bwd_fp32(int D, int rope, int mask, bool alibi, const BwdParams& p, hipStream_t st);
 int launch_decode(int D, int rope, bool alibi, const DecodeParams& p, hipStream_t st);
 int launch_rope(bool fp32, int D, int rope, bool inverse, const RopeParams& p, hipStream_t st);

@@ -1,0 +1,50 @@
+"""The dK/dV pass where several workgroups share a key block (fp32 partials and
+a reduction): gradients against the fp64 oracle at sizes whose steps do not
+divide evenly, with ragged last blocks, every RoPE kind and mask, ALiBi, a bias
+and relu weights, and nothing written past the workspace."""
+import pytest
+import torch
+
+import oracle
+from gpu_util import announce, assert_bf16_close, device_inputs, f64, need_gpu
+from paper_2609_13612_amd import api, inputs
+
+pytestmark = pytest.mark.gpu
+
+CASES = [(1, 8, 2, 600, 128, "neox", "causal", None, None), (2, 4, 1, 333, 128, "neox", "none", None, "softmax"),
+         (1, 8, 2, 1001, 64, "interleaved", "causal", None, None), (1, 6, 1, 515, 128, "none", "causal", None, None),
+         (2, 6, 1, 300, 64, "neox", "none", None, "relu"), (1, 8, 1, 700, 128, "interleaved", "sliding_window", 333, None)]
+
+
+@pytest.mark.parametrize("B,H,Hkv,S,D,rope,mask,window,norm", CASES, ids=lambda x: str(x))
+def test_split_gradients(B, H, Hkv, S, D, rope, mask, window, norm):
+    need_gpu()
+    announce(f"bwd splits {B} {H}/{Hkv} {S} {D} {rope} {mask} {norm}")
+    cpu, d = device_inputs(B, H, Hkv, S, D, seed=S, with_do=True)
+    kw = dict(rope=rope, mask=mask, window=window)
+    okw = dict(kw, theta=10000.0)
+    fwd, bwd = api.attnfuse_fwd, api.attnfuse_bwd
+    if norm:
+        bias = torch.randn(B, 1, 1, S, generator=torch.Generator().manual_seed(S))
+        scale = (1.0 if norm == "softmax" else 1.0 / S) / D ** 0.5
+        if norm == "relu":
+            bias = bias / S
+        kw.update(norm=norm, bias=bias.cuda(), scale=scale)
+        okw.update(norm=norm, bias=f64(bias.expand(B, H, S, S)), scale=scale)
+        if norm == "relu":
+            okw["relu_gate"] = "fp16"
+        fwd, bwd = api.attnfuse_fwd_bias_norm, api.attnfuse_bwd_bias_norm
+    elif rope == "none":
+        kw["alibi_slopes"] = inputs.alibi_slopes(H).cuda()
+        okw["alibi_slopes"] = f64(inputs.alibi_slopes(H))
+    n = api.attnfuse_bwd_workspace_bytes(B, H, Hkv, S, D, rope)
+    unsplit = 2 * B * S * D * (H + (H + Hkv if rope != "none" else 0)) + 8 * B * H * S + 16384
+    assert n > unsplit + 2 * 8 * B * Hkv * S * D - 1, "the case is meant to split"
+    o, lse = fwd(d["q"], d["k"], d["v"], **kw)
+    ws = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    g = bwd(d["q"], d["k"], d["v"], o, d["do"], lse, workspace=ws[:n], **kw)
+    torch.cuda.synchronize()
+    assert (ws[n:] == 0x5A).all(), "written past the workspace"
+    ref = oracle.attention_backward(*[f64(cpu[x]) for x in ("q", "k", "v", "do")], **okw)
+    for name, a, r in zip(("dQ", "dK", "dV"), g, ref):
+        assert_bf16_close(a, r, name)
