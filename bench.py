@@ -629,7 +629,7 @@ def main():
                                   f"{'forward + backward' if do_bwd else 'forward'}, fp64 numpy, full S={w.S}"}
         log(f"cpu oracle sample: {tb - ta:.1f} s")
 
-    roofline = {"bound": "mfma", "kernel": "fwd_bf16_kernel (fused RoPE + mask, one launch per forward)",
+    roofline = {"bound": "mfma", "kernel": "fwd_bf16_kernel (fused RoPE + mask) with the launch before it that rotates K once",
                 "achieved": round(fwd_tf, 1), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(fwd_tf / PEAK_BF16_TFLOPS, 4), "traffic": measured_traffic(w.name)}
 
