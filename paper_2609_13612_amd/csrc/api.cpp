@@ -172,19 +172,6 @@ DecodeLayout decode_layout(int B, int H, int H_kv, int S, int D) {
   return L;
 }
 
-// Pieces per K/V head when the sequences are cut by their lengths (one partial
-// each, in the room of nsplit chunks' four): the 512 workgroups of one resident
-// round, or four per sequence where the batch alone fills them.  0, the even
-// split, for one sequence and where a chunk is under 1024 rows of 256 bytes:
-// working out the pieces costs about 2 us (B8 H32/8, cache 2048: 19.8 us even,
-// 21.9 cut; B4 H64/8, cache 4000: 20.6 and 22.3; B16 H16 D64, cache 2000: 25.8
-// and 31.1; B12 H12/4 D128, cache 6000: 35.3 and 28.0).
-int decode_slots(const DecodeLayout& L, int B, int H_kv, int D) {
-  if (B < 2 || L.chunk * D < 1024 * 128) return 0;
-  const long long room = 4ll * B * L.nsplit, want = 512 / H_kv > 4ll * B ? 512 / H_kv : 4ll * B;
-  return (int)(room < want ? room : want);
-}
-
 // ---------------------------------------------------------------- shared bodies
 // Dense bias tensor and normalisation of the extended entry points (EXT_NONE
 // for the plain ones).
@@ -545,7 +532,6 @@ static int decode_impl(const void* Q, const void* K, const void* V, const int* c
   p.B = B; p.H = H; p.Hkv = H_kv; p.S = S_kv;
   p.window = (mask == AF_MASK_SLIDING_WINDOW) ? (window < S_kv ? window : S_kv) : 0;
   p.chunk = L.chunk; p.nsplit = L.nsplit;
-  p.slots = cache_lens ? decode_slots(L, B, H_kv, D) : 0;
   p.slopes = alibi_slopes;
   p.scale = softmax_scale;
   p.table = (rope != AF_ROPE_NONE) ? reinterpret_cast<const float2*>(rope_table) : nullptr;

@@ -80,86 +80,7 @@ __device__ __forceinline__ int first_key(const DecodeParams& p, int L) {
   return (p.window > 0) ? max(0, L - p.window) : 0;
 }
 
-// ---------------------------------------------------------------- caches of different lengths
-// With per-sequence lengths the even split of the longest possible cache
-// leaves the workgroups of short sequences idle while others stream.  Here
-// the pieces are sized from the lengths themselves: every sequence is cut into
-// pieces of `c` 32-key tiles, c (a multiple of 4, the waves' step) the smallest
-// (in steps of at most c / 16) for which all sequences together take at most
-// p.slots pieces per K/V head: one round of resident workgroups.
-// Every wave works this out for itself from the lengths (at most two loads per
-// 64 sequences): the grid is fixed by the host at slots x H_kv, and the
-// workgroups past the last piece return.  Even split / cut by length, us:
-// B4 H64/8 cache 32768, lengths {32768, 16384, 8192, 24000} 78.9 / 68.7,
-// {30000, 9000, 9000, 9000} 70.1 / 52.9; B6 H24/8, [8000, 32768] 122 / 80; B16
-// H32/8 cache 8192, [2048, 8192] 75.7 / 68.2; B64 cache 4096, [100, 4096] 147 / 134.
-__device__ __forceinline__ int visible_tiles(const DecodeParams& p, int b) {
-  const int L = (b < p.B) ? seq_len(p, b) : 0;
-  return L < 1 ? 0 : (L - (first_key(p, L) & ~31) + 31) / 32;
-}
-
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-
-// The wave's view of the plan: lane l holds sequence l's tiles (longer batches
-// read the rest again each time).
-struct Pieces {
-  int own;   // tiles of sequence `lane`
-  int c;     // tiles per piece
-  __device__ __forceinline__ int tiles(const DecodeParams& p, int b0, int lane) const {
-    return b0 == 0 ? own : visible_tiles(p, b0 + lane);
-  }
-  __device__ __forceinline__ int count(const DecodeParams& p, int b0, int lane) const {
-    return (tiles(p, b0, lane) + c - 1) / c;
-  }
-  __device__ __forceinline__ Pieces(const DecodeParams& p, int lane) : own(visible_tiles(p, lane)) {
-    int total = 0;
-    for (int b0 = 0; b0 < p.B; b0 += 64) total += tiles(p, b0, lane);
-    total = wave_sum(total);
-    // c doubles at most: at ceil(total / (slots - B)) the pieces fit for certain
-    const int sure = p.slots > p.B ? (total + p.slots - p.B - 1) / (p.slots - p.B) : 0x7ffffff0;
-    for (c = max(4, ((total + p.slots - 1) / p.slots + 3) & ~3); c < sure; c += max(4, (c >> 4) & ~3)) {
-      int n = 0;
-      for (int b0 = 0; b0 < p.B; b0 += 64) n += count(p, b0, lane);
-      if (wave_sum(n) <= p.slots) break;
-    }
-  }
-  // The sequence that piece r belongs to (b = -1: past the last) and the
-  // piece's index in it.
-  __device__ __forceinline__ void find(const DecodeParams& p, int r, int lane, int& b, int& piece) const {
-    int base = 0;
-    for (int b0 = 0; b0 < p.B; b0 += 64) {
-      const int n = count(p, b0, lane);
-      int incl = n;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int x = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += x;
-      }
-      const unsigned long long hit = __ballot(base + incl > r);
-      if (hit != 0ull) {
-        const int l = __ffsll((long long)hit) - 1;
-        b = b0 + l;
-        piece = r - base - (__shfl(incl, l, 64) - __shfl(n, l, 64));
-        return;
-      }
-      base += __shfl(incl, 63, 64);
-    }
-    b = -1;
-    piece = 0;
-  }
-  // Pieces of the sequences before b.
-  __device__ __forceinline__ int before(const DecodeParams& p, int b, int lane) const {
-    int n = 0;
-    for (int b0 = 0; b0 < b; b0 += 64) n += (b0 + lane < b) ? count(p, b0, lane) : 0;
-    return wave_sum(n);
-  }
-};
-
-template <int D, int ROPE, bool ALIBI, bool RAGGED>
+template <int D, int ROPE, bool ALIBI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void decode_split_kernel(DecodeParams p) {
   using C = DecCfg<D>;
@@ -169,28 +90,15 @@ void decode_split_kernel(DecodeParams p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, lg = lane >> 5;
+  const int split = (int)(blockIdx.x % p.nsplit);
+  const int unit = (int)(blockIdx.x / p.nsplit);
+  const int b = unit / p.Hkv, g = unit % p.Hkv;
   const int G = p.H / p.Hkv;
-  int b, g, split, chunk = p.chunk;
-  if constexpr (RAGGED) {
-    const Pieces pieces(p, lane);
-    pieces.find(p, (int)(blockIdx.x / p.Hkv), lane, b, split);
-    b = __builtin_amdgcn_readfirstlane(b);
-    split = __builtin_amdgcn_readfirstlane(split);
-    if (b < 0) return;                             // past the last piece (workgroup-uniform)
-    g = (int)(blockIdx.x % p.Hkv);
-    chunk = __builtin_amdgcn_readfirstlane(32 * pieces.c);
-  } else {
-    split = (int)(blockIdx.x % p.nsplit);
-    const int u = (int)(blockIdx.x / p.nsplit);
-    b = u / p.Hkv;
-    g = u % p.Hkv;
-  }
-  const int unit = b * p.Hkv + g;
   const int L = seq_len(p, b);
   if (L < 1) return;
   const int lo = first_key(p, L);
-  const int c0 = split * chunk + (RAGGED ? lo & ~31 : 0);
-  if (c0 + chunk <= lo || c0 >= L) return;         // no visible key in this chunk (workgroup-uniform)
+  const int c0 = split * p.chunk;
+  if (c0 + p.chunk <= lo || c0 >= L) return;       // no visible key in this chunk (workgroup-uniform)
   const int pos = L - 1;                           // the query's position
 
   const int hc = lq % G;                           // head of this lane's column (cyclic replication)
@@ -205,7 +113,7 @@ void decode_split_kernel(DecodeParams p) {
   // starting at the first tile that holds a visible key.
   constexpr int STEP = 32 * C::NW;
   const int first = lo & ~31;
-  const int kend = min(c0 + chunk, L);
+  const int kend = min(c0 + p.chunk, L);
   int kbeg = c0 + 32 * wave;
   if (kbeg < first) kbeg += (first - kbeg + STEP - 1) / STEP * STEP;
 
@@ -321,61 +229,8 @@ void decode_split_kernel(DecodeParams p) {
       }
   }
 
-  const float l_tot = pair_sum(l_run);
-  if constexpr (RAGGED) {
-    // One partial per piece (four times as many pieces fit the workspace as
-    // with one per wave): the waves add theirs in LDS in turn, over the V
-    // tiles, relative to the largest of their maxima.
-    __shared__ float wm[C::NW][32], wl[C::NW][32];
-    float* sum = reinterpret_cast<float*>(smem);   // [G][D]
-    static_assert(32 * D * sizeof(float) <= C::SMEM * sizeof(uint16_t), "the sums fit the V tiles");
-    if (lg == 0) {
-      wm[wave][lq] = m_run;
-      wl[wave][lq] = l_tot;
-    }
-    __syncthreads();
-    float m_all = wm[0][lq];
-#pragma unroll
-    for (int w = 1; w < C::NW; ++w) m_all = fmaxf(m_all, wm[w][lq]);
-    const float a = (m_run == -INFINITY) ? 0.f : fast_exp2(m_run - m_all);
-#pragma unroll
-    for (int w = 0; w < C::NW; ++w) {
-      if (wave == w && lq < G) {
-        float* dst = sum + lq * D + 4 * lg;
-#pragma unroll
-        for (int mt = 0; mt < C::MT; ++mt)
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            float4* d = reinterpret_cast<float4*>(dst + 32 * mt + 8 * q4);
-            float4 x = {a * acc[mt][4 * q4], a * acc[mt][4 * q4 + 1], a * acc[mt][4 * q4 + 2], a * acc[mt][4 * q4 + 3]};
-            if (w > 0) {
-              const float4 y = *d;
-              x = float4{x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w};
-            }
-            *d = x;
-          }
-      }
-      __syncthreads();
-    }
-    const int r = (int)(blockIdx.x / p.Hkv);
-    for (int i = tid; i < G * (D / 4); i += 256) {
-      const int hh = i / (D / 4), d4 = i % (D / 4);
-      const size_t prow = (size_t)(g * G + hh) * p.slots + r;
-      reinterpret_cast<float4*>(p.part_acc + prow * D)[d4] = reinterpret_cast<const float4*>(sum)[i];
-    }
-    if (tid < G) {
-      float m = -INFINITY, l = 0.f;
-#pragma unroll
-      for (int w = 0; w < C::NW; ++w) m = fmaxf(m, wm[w][tid]);
-#pragma unroll
-      for (int w = 0; w < C::NW; ++w) l += (wm[w][tid] == -INFINITY) ? 0.f : wl[w][tid] * fast_exp2(wm[w][tid] - m);
-      const size_t prow = (size_t)(g * G + tid) * p.slots + r;
-      p.part_ml[prow * 2] = m;
-      p.part_ml[prow * 2 + 1] = l;
-    }
-    return;
-  }
   // One partial per wave, straight from registers: the first G head columns.
+  const float l_tot = pair_sum(l_run);
   const int nslot = p.nsplit * C::NW;
   if (lq < G) {
     const size_t prow = ((size_t)b * p.H + g * G + lq) * nslot + split * C::NW + wave;
@@ -408,7 +263,7 @@ __device__ __forceinline__ void merge_ml(float& m, float& l, float m2, float l2)
 // one round trip to memory: each thread folds the (m, l) pairs it reads into
 // a running pair, the pairs merge across the workgroup, and every thread
 // weights its accumulators by 2^(m_s - M).
-template <int D, int PF, bool RAGGED>
+template <int D, int PF>
 __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
   __shared__ float red[256];
   __shared__ float wred[8];
@@ -422,20 +277,12 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
     if (t == 0 && blockIdx.y == 0) p.lse[bh] = -INFINITY;
     return;
   }
-  int n;            // partials of this head, from row `row` of the workspace
-  size_t row;
-  if constexpr (RAGGED) {
-    const Pieces pieces(p, lane);
-    n = (visible_tiles(p, b) + pieces.c - 1) / pieces.c;
-    row = (size_t)(bh % p.H) * p.slots + pieces.before(p, b, lane);
-  } else {
-    constexpr int NWV = DecCfg<D>::NW;   // partials per chunk
-    const int s_lo = first_key(p, L) / p.chunk, s_hi = (L - 1) / p.chunk;
-    n = (s_hi - s_lo + 1) * NWV;
-    row = (size_t)bh * p.nsplit * NWV + s_lo * NWV;
-  }
-  const float* ml = p.part_ml + row * 2;
-  const float* acc = p.part_acc + row * D + d;
+  constexpr int NWV = DecCfg<D>::NW;   // partials per chunk
+  const int nslot = p.nsplit * NWV;
+  const int s_lo = first_key(p, L) / p.chunk, s_hi = (L - 1) / p.chunk;
+  const int n = (s_hi - s_lo + 1) * NWV;
+  const float* ml = p.part_ml + ((size_t)bh * nslot + s_lo * NWV) * 2;
+  const float* acc = p.part_acc + ((size_t)bh * nslot + s_lo * NWV) * D + d;
   float a[PF], mm[PF];
 #pragma unroll
   for (int j = 0; j < PF; ++j) {
@@ -476,20 +323,14 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
 
 template <int D, int ROPE, bool ALIBI>
 static int launch_one(const DecodeParams& p, hipStream_t st) {
-  const dim3 cgrid((unsigned)(p.B * p.H), D / 32);
-  if (p.slots > 0) {   // sequences of different lengths
-    hipLaunchKernelGGL((decode_split_kernel<D, ROPE, ALIBI, true>), dim3((unsigned)(p.slots * p.Hkv)), dim3(256), 0, st,
-                       p);
-    hipLaunchKernelGGL((decode_combine_kernel<D, 16, true>), cgrid, dim3(256), 0, st, p);
-    return hipGetLastError() == hipSuccess ? 0 : -3;
-  }
   const long long blocks = (long long)p.nsplit * p.B * p.Hkv;
-  hipLaunchKernelGGL((decode_split_kernel<D, ROPE, ALIBI, false>), dim3((unsigned)blocks), dim3(256), 0, st, p);
+  hipLaunchKernelGGL((decode_split_kernel<D, ROPE, ALIBI>), dim3((unsigned)blocks), dim3(256), 0, st, p);
   // preload depth: every partial of a head (8 groups x PF) when it fits
+  const dim3 cgrid((unsigned)(p.B * p.H), D / 32);
   if (p.nsplit * DecCfg<D>::NW <= 8 * 16)
-    hipLaunchKernelGGL((decode_combine_kernel<D, 16, false>), cgrid, dim3(256), 0, st, p);
+    hipLaunchKernelGGL((decode_combine_kernel<D, 16>), cgrid, dim3(256), 0, st, p);
   else
-    hipLaunchKernelGGL((decode_combine_kernel<D, 32, false>), cgrid, dim3(256), 0, st, p);
+    hipLaunchKernelGGL((decode_combine_kernel<D, 32>), cgrid, dim3(256), 0, st, p);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 

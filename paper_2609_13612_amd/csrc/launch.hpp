@@ -76,7 +76,6 @@ struct DecodeParams {
   int B, H, Hkv, S;
   int window;             // > 0: sliding window of that many keys; 0: every cached key
   int chunk, nsplit;      // keys per phase-1 workgroup; chunks per sequence
-  int slots;              // > 0: cut the sequences by their lengths into at most this many pieces per K/V head
   const float* slopes;
   float scale;
   const float2* table;

@@ -1,8 +1,8 @@
-"""Decode over caches of different lengths, where the sequences are cut into
-pieces by their lengths (batches whose even chunks would be long): against the
-fp64 oracle, with lengths at the edges of tiles and pieces, empty and over-long
-ones, a window, more sequences than a wave has lanes, and workspaces of exactly
-the size the library asks for."""
+"""Decode over caches of different lengths: against the fp64 oracle, with
+lengths at the edges of tiles and chunks, empty and over-long ones, a window,
+more sequences than a wave has lanes, and workspaces of exactly the size the
+library asks for; and each sequence's result the same bits whatever the lengths
+of the others."""
 import numpy as np
 import pytest
 import torch
@@ -47,3 +47,26 @@ def test_cut_by_length(B, H, Hkv, S, D, lens, mask, window, alibi, rope):
     got = f64(lse)
     assert np.array_equal(np.isinf(got), np.isinf(L))
     assert_lse_close(lse[live], L[live], "LSE")
+
+
+@pytest.mark.parametrize("B,H,Hkv,S,D", [(4, 8, 4, 18000, 128), (3, 16, 16, 20000, 64), (70, 8, 2, 4000, 128)])
+def test_a_sequence_does_not_depend_on_the_others(B, H, Hkv, S, D):
+    """The same cache and length beside other lengths, and full lengths beside none given: the same bits, also in a
+    workspace that holds something else."""
+    need_gpu()
+    announce(f"decode neighbours B={B} H={H}/{Hkv} S={S} D={D}")
+    c = inputs.make_decode(B, H, Hkv, S, D, seed=S)
+    dev = {n: c[n].cuda() for n in ("q", "k", "v")}
+
+    def run(lens, fill):
+        ws = torch.full((api.attnfuse_decode_workspace_bytes(B, H, Hkv, S, D),), fill, dtype=torch.uint8, device="cuda")
+        ln = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+        return api.attnfuse_decode(dev["q"], dev["k"], dev["v"], ln, rope="neox", workspace=ws)
+
+    own = 2 * S // 3 + 5
+    want = run([own] + [S] * (B - 1), 0)
+    for others in ([1] * (B - 1), [0] * (B - 1), [(37 * b) % S for b in range(1, B)]):
+        got = run([own] + others, 0xFF)
+        assert torch.equal(got[0][0], want[0][0]) and torch.equal(got[1][0], want[1][0])
+    for x, y in zip(run(None, 0), run([S] * B, 0xFF)):
+        assert torch.equal(x, y)
