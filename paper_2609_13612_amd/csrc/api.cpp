@@ -306,7 +306,54 @@ int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const v
   return map_launch(af::launch_bwd_bf16(D, rope, mask, alibi, ext.kind(), p, st));
 }
 
+// Query heads per workgroup, as the launchers pack them.
+int heads_packed(int G, int max) {
+  int hp = 1;
+  while (hp < max && G % (2 * hp) == 0) hp *= 2;
+  return hp;
+}
+
 }  // namespace
+
+// Four waves (128 rows, two or three workgroups per CU that do not wait at each
+// other's barriers) against eight (256 rows share each staged tile), us:
+//   tiles copied to LDS, D = 128: B1 H32/8 causal S 500 / 2048 / 8192: 14.5 / 47.6 / 523 with four, 20.1 / 56.0 /
+//   515 with eight; B4 H32/8 S8192 window 1024: 602 and 625; D = 64: B8 H16 S2048 causal 97 and 108, B4 H12 S2048
+//   no mask 65 and 78.
+// Past about 6000 keys per row at D = 128 the second copy of every tile costs
+// more than the finer workgroups give.  So it does where the finer workgroups
+// finish no sooner, all being equal without a mask: D = 64 B1 H12 S4096 76.1 with
+// four, 73.3 with eight (staged through registers; 96.3 and 91.4 with a key bias),
+// D = 128 with a key bias, whose loads wait for the copies, B1 H16/4 S3000 97.3 and 85.8,
+// S2048 H32/8 77.0 and 71.9, causal S4096 159 and 145.  (With a bias row per query
+// four win: D = 64 B2 H16 S2048 72.5 and 93.)  Rotating in the loop doubles that work
+// too.  There four waves win on short rows while their workgroups fit one round
+// of the CUs (8 to 40 % at S 64 to 512 with D = 128, to 1024 with D = 64; from S
+// 350 the interleaved form at D = 128 lost 1 to 9 %, its four-wave kernel spills).
+// In more than a round they lose 10 to 28 % without a mask (B6 H16/2 S400 D128
+// 29.9 and 38.0, B3 H12 S1000 D64 30.4 and 34.4), and win only
+//   with a causal mask at D = 64 (4 to 14 %) or, NeoX, over 128 to 256 rows (0 to 9 %);
+//   under a window whose edges the finer rows cut: 8 to 50 % where a workgroup visits at most three quarters of the
+//   tiles (window 100, one head per workgroup), otherwise they lose up to 14 %.
+int af::fwd_waves(int B, int H, int Hkv, int S, int D, int rope, int mask, int window, int bias) {
+  const int G = H / Hkv, rows4 = 128 / heads_packed(G, 4), rows8 = 256 / heads_packed(G, 8);
+  const bool cut = mask == AF_MASK_SLIDING_WINDOW;
+  const long long n4 = (long long)((S + rows4 - 1) / rows4) * B * (H / heads_packed(G, 4));
+  const long long n8 = (long long)((S + rows8 - 1) / rows8) * B * (H / heads_packed(G, 8));
+  if (rope == AF_ROPE_NONE) {   // copied to LDS
+    if (D == 64) return mask == AF_MASK_NONE && bias < 2 && n4 > 256 && n4 <= 512 && S >= (bias ? 1024 : 2048) ? 8 : 4;
+    if (bias == 1 && mask == AF_MASK_NONE && (n4 + 255) / 256 >= 2 * ((n8 + 255) / 256)) return 8;
+    if (bias == 1 && mask == AF_MASK_CAUSAL && n8 >= 512 && S >= 2048) return 8;
+    return S < 6144 ? 4 : 8;
+  }
+  if (S > (D == 64 ? 1024 : rope == AF_ROPE_INTERLEAVED && !cut ? 256 : 512)) return 8;
+  if (n4 <= 256) return 4;
+  if (n8 >= 256 || mask == AF_MASK_NONE) return 8;
+  if (!cut) return D == 64 || (rope == AF_ROPE_NEOX && S >= 128 && S <= 256 && rows4 < rows8) ? 4 : 8;
+  const double nt = (S + 63) / 64;
+  const auto tiles = [&](int rows) { return std::fmin(nt, (rows + (double)window) / 64.0 + 1.0); };
+  return tiles(rows4) <= 0.75 * tiles(rows8) ? 4 : 8;
+}
 
 extern "C" {
 
@@ -392,8 +439,7 @@ size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, i
     return 0;
   const size_t bytes = (size_t)B * H_kv * S * D * 2;
   const int G = H / H_kv;
-  int hp = 1;                       // query heads per workgroup, as the launcher packs them
-  while (hp < (sparse_blocks ? 4 : 8) && G % (2 * hp) == 0) hp *= 2;
+  const int hp = heads_packed(G, sparse_blocks ? 4 : 8);
   const double units = (double)B * H_kv * (G / hp);
   const double nt = (S + 63) / 64;
   double saved;
@@ -413,6 +459,10 @@ size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, i
     else saved = 5.0 * (turns - 1.0) + (D == 128 ? 0.3 : 0.2) * load;
   }
   return saved > 2.6 + (double)bytes * 2.0 / 4.5e6 ? bytes : 0;
+}
+
+int af_fwd_waves(int B, int H, int H_kv, int S, int D, int rope, int mask, int window, int bias) {
+  return af::fwd_waves(B, H, H_kv, S, D, rope, mask, window, bias);
 }
 
 int af_fwd_ws(const void* Q, const void* K, const void* V, void* O, float* LSE, const int* q_block_ptr,

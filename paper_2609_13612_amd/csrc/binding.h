@@ -18,6 +18,11 @@ extern "C" {
 size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, int rope, int mask, int window,
                               int norm, long long sparse_blocks);
 
+/* Waves per workgroup (4 or 8) of the dense forward of these sizes where both
+ * forms exist; rope: AF_ROPE_NONE for tiles that are not rotated in the loop;
+ * bias: 0 without one, 1 where one row serves every query, 2 a row per query. */
+int af_fwd_waves(int B, int H, int H_kv, int S, int D, int rope, int mask, int window, int bias);
+
 /* attnfuse_fwd (bias == NULL, q_block_ptr == NULL), attnfuse_fwd_bias_norm or
  * attnfuse_fwd_blocksparse with RoPE on bf16 tensors, given
  * 2 * B * H_kv * S * D bytes of 16-byte aligned device scratch; same results. */

@@ -70,8 +70,9 @@ void fwd_bf16_kernel(FwdParams p) {
   // Relu weights are unnormalised (not bounded by 1): P and V go to the PV
   // MFMA as fp16 (2^-12 rounding of P instead of bf16's 2^-9).
   // tiles that need no arithmetic on their way to LDS are copied there
-  // directly (relu attention converts V; block-sparse keeps its register sets)
-  constexpr bool ASYNC = KROPE == ROPE_NONE && !SPARSE && !RELU;
+  // directly (relu attention converts V; block-sparse keeps its register sets;
+  // at D = 64 eight waves are taken where staging through registers wins)
+  constexpr bool ASYNC = KROPE == ROPE_NONE && !SPARSE && !RELU && !(D == 64 && NW == 8);
   using AT = AsyncTile<D, NW>;
   constexpr int STAGES = ASYNC ? 4 * AT::ELEMS : (SPARSE ? 4 : 2) * C::STAGE;
   constexpr int OUT = NW * OUT_ROWS_ELEMS<D>;   // the output rows leave through the same memory
@@ -563,24 +564,6 @@ void fwd_bf16_kernel(FwdParams p) {
   }
 }
 
-// Waves per workgroup of a dense forward.  Four (128 rows, two or three
-// workgroups per CU that do not wait at each other's barriers) against eight
-// (256 rows share each staged tile), measured with tiles copied to LDS:
-//   D = 128: B1 H32/8 causal S 500 / 2048 / 8192: 14.5 / 47.6 / 523 us with four, 20.1 / 56.0 / 515 with eight;
-//   B4 H32/8 S8192 window 1024: 602 and 625; D = 64: B8 H16 S2048 causal 97 and 108, B4 H12 S2048 no mask 65 and 78.
-// Past about 6000 keys per row at D = 128 the second copy of every tile costs
-// more than the finer workgroups give.  Rotating in the loop doubles that work
-// too, so there four waves pay only for short rows that leave CUs without an
-// eight-wave workgroup: B4 H12 D64 S 512 / 1024 14.0 / 24.0 and 17.2 / 27.2 us,
-// H32/8 D128 S 256 / 512 15.0 / 23.4 and 18.3 / 26.0, but H16 D128 S1000 44.6 and
-// 37.9.  (Slopes and bias tensors spill in that form and stay with eight.)
-template <int D, bool ASYNC>
-bool fwd_four_waves(const FwdParams& p) {
-  if (ASYNC) return p.S < 6144;
-  const int hp = heads_per_wg(p.H / p.Hkv), rows = 256 / hp;
-  return p.S <= (D == 64 ? 1024 : 512) && (long long)((p.S + rows - 1) / rows) * p.B * (p.H / hp) < 256;
-}
-
 // One launch: a block-sparse or a dense forward.
 template <int D, int ROPE, int MASK, bool ALIBI, int EXT, bool KPRE>
 int fwd_launch_one(const FwdParams& p0, hipStream_t st) {
@@ -601,10 +584,12 @@ int fwd_launch_one(const FwdParams& p0, hipStream_t st) {
     hipLaunchKernelGGL((fwd_bf16_kernel<D, ROPE, MASK, ALIBI, true, EXT_NONE, KPRE, 8>), dim3((unsigned)blocks),
                        dim3(512), 0, st, p);
   } else {
-    constexpr bool ALWAYS4 = ASYNC && (D == 64 || MASK == MASK_SLIDING_WINDOW);
+    constexpr bool REG8 = D == 64 && ROPE == ROPE_NONE && MASK == MASK_NONE && !ALIBI;   // eight waves, staged
+    constexpr bool ALWAYS4 = ASYNC && !REG8 && (D == 64 || MASK == MASK_SLIDING_WINDOW);
     constexpr bool EITHER = !ALWAYS4 && (ASYNC || (EXT == EXT_NONE && !ALIBI));
     if constexpr (ALWAYS4 || EITHER) {
-      if (ALWAYS4 || fwd_four_waves<D, ASYNC>(p)) {
+      if (ALWAYS4 || fwd_waves(p.B, p.H, p.Hkv, p.S, D, ASYNC ? ROPE_NONE : ROPE, MASK, p.window,
+                                         !p.bias ? 0 : p.bias_sq == 0 ? 1 : 2) == 4) {
         launch(fwd_bf16_kernel<D, ROPE, MASK, ALIBI, false, EXT, KPRE, 4>, 4, 128, 4);
         return hipGetLastError() == hipSuccess ? 0 : -3;
       }

@@ -88,6 +88,12 @@ struct RopeParams {
   const float2* table;
 };
 
+// Waves per workgroup, four or eight, of a dense bf16 forward that has both
+// forms; rope: the rotation of its key tiles in the loop (ROPE_NONE where they
+// are copied to LDS as they are); bias: 0 without one, 1 where one row serves
+// every query, 2 a row per query.
+int fwd_waves(int B, int H, int Hkv, int S, int D, int rope, int mask, int window, int bias);
+
 // Return 0 on success, -2 when the variant is not compiled, -3 on a HIP error.
 // ext: EXT_* (common.hpp); variants other than EXT_NONE run without ALiBi and block masks.
 int launch_fwd_bf16(int D, int rope, int mask, bool alibi, int ext, const FwdParams& p, hipStream_t st);
