@@ -429,9 +429,14 @@ int attnfuse_fwd_bias_norm(const void* Q, const void* K, const void* V, void* O,
 //   D = 64, H12 B4 causal, S 512 / 1024 / 2048 / 4096: 13.4 / 15.7, 23.4 / 24.5, 48.5 / 49.5, 160 / 136; no mask 2048:
 //   89.6 / 73.5; window 256 at 4096: 58.5 / 47.1; B32 H16 S512: 58.5 / 55.2;
 //   block-sparse (9.2 % active) B4 H12 S4096 D64: 123 / 82; relu attention gains the rotation alone.
-// The saving follows the tiles of the longest workgroup while 256-row
-// workgroups leave CUs free, and otherwise the workgroups each CU takes in turn
-// (5 us each) and the tiles of the busiest CU.
+// An estimate in terms of 256-row workgroups, whichever form then runs: the
+// saving follows the tiles of the longest workgroup while these leave CUs free,
+// and otherwise the workgroups each CU takes in turn (5 us each) and the tiles of
+// the busiest CU.  It is smaller where four waves rotate in the loop (D = 64) and
+// where the copied form's four-wave workgroups take more than a round, unless a
+// causal mask or a window cuts their tiles: D = 64 B2 H16 S2048 no mask 49.4 / 52.8,
+// B1 H12 S4096 83.0 / 85.6, B1 H8/2 S5066 window 827 26.2 / 27.7, but B2 H8/2 S4085 no
+// mask 93.8 / 90.5; D = 128 B2 H16/4 S2048 window 300 26.2 / 28.1, but window 1024 45.1 / 44.1.
 size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, int rope, int mask, int window,
                               int norm, long long sparse_blocks) {
   if (B < 1 || H < 1 || H_kv < 1 || S < 1 || S > kMaxS || H % H_kv || !supported_d(D) || dtype != AF_DTYPE_BF16 ||
@@ -454,9 +459,17 @@ size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, i
       tiles = std::fmin(wgs * (nt + rows / 64.0) / 2.0, wgs * longest);
     }
     const double turns = units * wgs / 256.0, load = std::fmax(longest, units * tiles / 256.0);
-    if (norm == AF_NORM_RELU) saved = (D == 128 ? 0.27 : 0.135) * load;
-    else if (turns <= 1.0) saved = (D == 128 ? 0.8 : 0.25) * longest;
-    else saved = 5.0 * (turns - 1.0) + (D == 128 ? 0.3 : 0.2) * load;
+    if (norm == AF_NORM_RELU) {
+      saved = (D == 128 ? 0.27 : 0.135) * load;
+    } else if (turns <= 1.0) {
+      const double rows4 = 128.0 / heads_packed(G, 4), n4 = std::ceil(S / rows4) * B * (H / heads_packed(G, 4));
+      if (n4 > 256 && mask == AF_MASK_NONE) saved = D == 128 ? 2.0 + 0.22 * longest : 0.08 * longest;
+      else if (n4 > 256 && mask == AF_MASK_SLIDING_WINDOW && hp > 1) saved = D == 128 ? 2.0 + 0.22 * longest : 0.2 * longest;
+      else if (D == 128) saved = 0.8 * longest;
+      else saved = (af::fwd_waves(B, H, H_kv, S, D, rope, mask, window, 0) == 4 ? 0.16 : 0.25) * longest;
+    } else {
+      saved = 5.0 * (turns - 1.0) + (D == 128 ? 0.3 : 0.2) * load;
+    }
   }
   return saved > 2.6 + (double)bytes * 2.0 / 4.5e6 ? bytes : 0;
 }
