@@ -228,7 +228,9 @@ int attnfuse_fwd_blocksparse(const void* Q, const void* K, const void* V, void* 
  *   k_block_ptr  device int32 [nb + 1], q_block_idx: key-block column c's
  *                active query blocks (compressed sparse column form)
  * The two lists must describe the same block set; no check is made that they
- * do.  Workspace, other arguments and results as attnfuse_bwd; bf16 only.
+ * do.  Workspace, other arguments and results as attnfuse_bwd; bf16 only.  One
+ * workgroup takes each key block: from the lists' addresses the library cannot
+ * tell whether sharing it would pay.
  */
 int attnfuse_bwd_blocksparse(const void* Q, const void* K, const void* V, const void* O, const void* dO,
                              const float* LSE, void* dQ, void* dK, void* dV,

@@ -250,7 +250,7 @@ def attnfuse_bwd(q, k, v, o, do, lse, *, rope="none", theta=10000.0, mask="causa
     """dQ, dK, dV of attnfuse_fwd; see attnfuse_bwd in include/attnfuse.h."""
     if _native is not None:
         r = _native.bwd(q, k, v, o, do, lse, dq, dk, dv, workspace, alibi_slopes, rope_table, _TABLES,
-                        ROPE.get(rope, -1), theta, MASK.get(mask, -1), window, scale, 0, 0, 0, 0, 0, 0, 0, 0, 0)
+                        ROPE.get(rope, -1), theta, MASK.get(mask, -1), window, scale, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0)
         if r is not None:
             return _result(r, "attnfuse_bwd")
     dev = _device(q)
@@ -328,9 +328,11 @@ def attnfuse_bwd_blocksparse(q, k, v, o, do, lse, block_mask, *, rope="none", th
     B, H, Hkv, S, D = _shape(q, k)
     _bwd_inputs(q, k, v, o, do, lse, dev, lse_needed=True)
     qp, ki, kp, qi = _mask_ptrs(block_mask, q, S)
+    longest, tiles = (block_mask.col_tiles or ((0, 0), (0, 0)))[mask != "none"]
     if _native is not None:
         r = _native.bwd(q, k, v, o, do, lse, dq, dk, dv, workspace, alibi_slopes, rope_table, _TABLES,
-                        ROPE.get(rope, -1), theta, MASK.get(mask, -1), window, scale, 0, 0, 0, 0, 0, qp, ki, kp, qi)
+                        ROPE.get(rope, -1), theta, MASK.get(mask, -1), window, scale, 0, 0, 0, 0, 0, qp, ki, kp, qi,
+                        longest, tiles)
         if r is not None:
             return _result(r, "attnfuse_bwd_blocksparse")
     dq, dk, dv = _grads(q, k, dq, dk, dv, dev)
@@ -339,10 +341,10 @@ def attnfuse_bwd_blocksparse(q, k, v, o, do, lse, block_mask, *, rope="none", th
     tab = _table(rope, theta, D, S, dev, rope_table)
     tp, tr = _tab(tab)
     with torch.cuda.device(dev):
-        code = _lib.load().attnfuse_bwd_blocksparse(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(do), _ptr(lse),
-                                                    _ptr(dq), _ptr(dk), _ptr(dv), qp, ki, kp, qi, _ptr(workspace),
-                                                    wbytes, B, H, Hkv, S, D, DTYPE[q.dtype], r, th, tp, tr, m, w,
-                                                    _ptr(alibi_slopes), sc, _stream())
+        code = _lib.load().af_bwd_blocksparse(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(do), _ptr(lse), _ptr(dq),
+                                              _ptr(dk), _ptr(dv), qp, ki, kp, qi, longest, tiles, _ptr(workspace),
+                                              wbytes, B, H, Hkv, S, D, DTYPE[q.dtype], r, th, tp, tr, m, w,
+                                              _ptr(alibi_slopes), sc, _stream())
     _check(code, "attnfuse_bwd_blocksparse")
     return dq, dk, dv
 
@@ -410,7 +412,7 @@ def attnfuse_bwd_bias_norm(q, k, v, o, do, lse, *, bias=None, norm="softmax", ro
     if _native is not None:
         r = _native.bwd(q, k, v, o, do, lse, dq, dk, dv, workspace, None, rope_table, _TABLES, ROPE.get(rope, -1),
                         theta, MASK.get(mask, -1), window, scale, *_bias_args(bias, q, B, H, S), NORM.get(norm, -1),
-                        0, 0, 0, 0)
+                        0, 0, 0, 0, 0, 0)
         if r is not None:
             return _result(r, "attnfuse_bwd_bias_norm")
     _bwd_inputs(q, k, v, o, do, lse, dev, lse_needed=NORM[norm] == NORM["softmax"])

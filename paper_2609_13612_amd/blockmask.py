@@ -28,13 +28,17 @@ class BlockMask:
 
     ``active`` is the bool matrix [nb, nb] (on the lists' device); the four
     int32 tensors are the compressed lists, each row's / column's entries
-    ascending."""
+    ascending.  ``col_tiles`` says how long the column lists are, for the dK/dV
+    pass: (longest, all) of the query blocks that two neighbouring key blocks
+    visit together, over the whole matrix and over its lower triangle; None if
+    not known."""
     S: int
     active: torch.Tensor
     q_ptr: torch.Tensor
     k_idx: torch.Tensor
     k_ptr: torch.Tensor
     q_idx: torch.Tensor
+    col_tiles: tuple = None
 
     @property
     def nb(self):
@@ -50,7 +54,7 @@ class BlockMask:
 
     def to(self, device):
         return BlockMask(self.S, *(t.to(device) for t in (self.active, self.q_ptr, self.k_idx, self.k_ptr,
-                                                           self.q_idx)))
+                                                           self.q_idx)), self.col_tiles)
 
     def as_oracle(self):
         """The (block size, bool numpy matrix) pair the oracle takes."""
@@ -66,6 +70,17 @@ def _compress(active):
     return ptr.to(torch.int32).contiguous(), idx.to(torch.int32).contiguous()
 
 
+def _col_tiles(active):
+    """BlockMask.col_tiles of a bool matrix."""
+    res = []
+    for a in (active, active.tril()):
+        a = torch.nn.functional.pad(a, (0, a.shape[1] % 2))
+        n = (a[:, 0::2] | a[:, 1::2]).sum(dim=0)
+        res += [n.max(), n.sum()]
+    longest, tiles, longest_lower, tiles_lower = torch.stack(res).tolist()
+    return (longest, tiles), (longest_lower, tiles_lower)
+
+
 def block_mask_from_dense(active, S, device=None):
     """BlockMask from a bool matrix [nb, nb] with nb = ceil(S / 64)."""
     active = torch.as_tensor(active, dtype=torch.bool)
@@ -74,12 +89,13 @@ def block_mask_from_dense(active, S, device=None):
         raise ValueError(f"block-sparse attention needs 1 <= S <= {BLOCK * MAX_BLOCKS}")
     if active.shape != (nb, nb):
         raise ValueError(f"active must be [{nb}, {nb}] for S={S}")
+    col_tiles = _col_tiles(active)
     if device is not None:
         active = active.to(device)
     active = active.contiguous()
     q_ptr, k_idx = _compress(active)
     k_ptr, q_idx = _compress(active.t().contiguous())
-    return BlockMask(S, active, q_ptr, k_idx, k_ptr, q_idx)
+    return BlockMask(S, active, q_ptr, k_idx, k_ptr, q_idx, col_tiles)
 
 
 def create_block_mask(predicate, S, device=None):

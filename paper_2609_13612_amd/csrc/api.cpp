@@ -81,6 +81,8 @@ bool supported_d(int D) { return D == 64 || D == 128; }
 // without / with, us: H32/8 D128 causal B1 S 256 / 512 / 1024 / 2048 / 4096 58 /
 // 95 / 167 / 340 / 782 and 44 / 56 / 91 / 202 / 582; B3 H16/4 S1777 no mask 404 and
 // 366; B2 H8/2 S4000 D64 causal 364 and 195.
+double split_us(double units, int S, int D) { return units * S * D * 4.0 * 2 * 2 / 4.5e6; }   // a split's dK' and dV, out and in
+
 int bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window) {
   const int G = H / H_kv, BQ = D == 64 ? 128 : 64;
   const double nkb = (S + 127) / 128, nt = (S + BQ - 1) / BQ, units = (double)B * H_kv;
@@ -92,7 +94,6 @@ int bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window) {
   }
   longest *= G;
   const double share = sum * G * units / 256.0, step = D == 64 ? 3.0 : 2.2;
-  const double part_us = units * S * D * 4.0 * 2 * 2 / 4.5e6;   // of one split: dK' and dV, out and in
   double best = 0.0, first = 0.0;
   int n = 1;
   for (int k : {1, 2, 3, 4, 6, 8}) {
@@ -100,7 +101,40 @@ int bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window) {
     const double each = std::ceil(longest / k);
     double us = step * (mask == AF_MASK_CAUSAL ? std::fmax(each, share) : std::ceil(nkb * units * k / 256.0) * each);
     if (k == 1) best = first = us;
-    else if ((us += 4.0 + k * part_us) < best && us < 0.9 * first) best = us, n = k;
+    else if ((us += 4.0 + k * split_us(units, S, D)) < best && us < 0.9 * first) best = us, n = k;
+  }
+  return n;
+}
+
+// The same under a block mask, from its lists: the 64-row query tiles that the
+// longest 128-key block visits, and all of them, as af_bwd_blocksparse is told
+// (0: not known).  Every workgroup spends 8 us on its list and resident rows, so
+// the pass ends with the longest or with the chip's share of the steps and
+// set-ups; at most `most`, what the dense call of the sizes takes.  All active:
+// as the dense call, whose sums it then equals.  Whole backward unsplit / as the
+// dense call / by the lists, us, causal: B1 H8 S2000 D128, diagonal blocks 55 / 81 /
+// 55, 10 % random 87 / 96 / 87; B1 H32/8 S2048 D128 diagonal 73 / 90 / 73, BigBird
+// (global block) 325 / 143 / 143; B1 H4/1 S8000 D128 10 % random 332 / 152 / 152.
+int bwd_splits_sparse(int B, int H, int H_kv, int S, int D, int mask, int window, int longest_list, long long tiles,
+                      int most) {
+  if (longest_list < 1 || tiles < 1) return 1;
+  const int G = H / H_kv;
+  const long long nkb = (S + 127) / 128, nt = (S + 63) / 64;
+  if (tiles == (mask == AF_MASK_NONE ? nkb * nt : nkb * nt - nkb * (nkb - 1))) return most;
+  const double units = (double)B * H_kv, step = D == 64 ? 1.5 : 2.2, setup = 8.0;
+  double longest = longest_list, sum = (double)tiles;
+  if (mask == AF_MASK_SLIDING_WINDOW) {
+    longest = std::fmin(longest, (128.0 + window) / 64.0 + 1.0);
+    sum = std::fmin(sum, (double)nkb * longest);
+  }
+  double best = 0.0, first = 0.0;
+  int n = 1;
+  for (int k : {1, 2, 3, 4, 6, 8}) {
+    if (k > longest * G || k > most) break;
+    double us = std::fmax(setup + step * std::ceil(longest * G / k),
+                          units * (nkb * k * setup + G * sum * step) / 256.0);
+    if (k == 1) best = first = us;
+    else if ((us += 4.0 + k * split_us(units, S, D)) < best && us < 0.9 * first) best = us, n = k;
   }
   return n;
 }
@@ -243,9 +277,15 @@ int fwd_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, c
   return map_launch(af::launch_fwd_fp32(D, rope, mask, alibi, p, st));
 }
 
-// sparse: NULL (dense) or {q_block_ptr, k_block_idx, k_block_ptr, q_block_idx}
+// A block mask's four lists (none of a dense call) and the lengths of its column lists (0: not known).
+struct Sparse {
+  const int *q_block_ptr, *k_block_idx, *k_block_ptr, *q_block_idx;
+  int longest = 0;
+  long long tiles = 0;
+};
+
 int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE, void* dQ,
-             void* dK, void* dV, const int* const* sparse, const Ext& ext, void* workspace, size_t workspace_bytes,
+             void* dK, void* dV, const Sparse* sparse, const Ext& ext, void* workspace, size_t workspace_bytes,
              int B, int H, int H_kv, int S, int D, int dtype, int rope, float rope_theta, const float* rope_table,
              int rope_table_rows, int mask, int window, const float* alibi_slopes, float softmax_scale,
              void* stream) {
@@ -281,9 +321,10 @@ int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const v
   p.dscale = reinterpret_cast<float*>(wb + ws.dscale);
   p.dmax = reinterpret_cast<uint32_t*>(wb + ws.dmax);
   p.splits = 1;
-  if (dtype == AF_DTYPE_BF16) {   // (a block mask: as without one, whose sums it then equals where all is active)
-    const int n = bwd_splits(B, H, H_kv, S, D, mask, window < S ? window : S);
-    p.splits = n < ws.splits ? n : ws.splits;
+  if (dtype == AF_DTYPE_BF16) {
+    const int w = window < S ? window : S, dense = bwd_splits(B, H, H_kv, S, D, mask, w);
+    const int n = dense < ws.splits ? dense : ws.splits;
+    p.splits = sparse ? bwd_splits_sparse(B, H, H_kv, S, D, mask, w, sparse->longest, sparse->tiles, n) : n;
     p.part = reinterpret_cast<float*>(wb + ws.part);
   }
   p.dmax_chunks = ws.dmax_chunks < af::DMAX_PARTS ? ws.dmax_chunks : af::DMAX_PARTS;
@@ -296,8 +337,8 @@ int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const v
   p.scale = softmax_scale;
   p.table = (rope != AF_ROPE_NONE) ? reinterpret_cast<const float2*>(rope_table) : nullptr;
   if (sparse) {
-    p.bq_ptr = sparse[0]; p.bk_idx = sparse[1];
-    p.bk_ptr = sparse[2]; p.bq_idx = sparse[3];
+    p.bq_ptr = sparse->q_block_ptr; p.bk_idx = sparse->k_block_idx;
+    p.bk_ptr = sparse->k_block_ptr; p.bq_idx = sparse->q_block_idx;
   }
   p.bias = ext.bias;
   p.bias_sb = ext.sb; p.bias_sh = ext.sh; p.bias_sq = ext.sq;
@@ -517,6 +558,26 @@ int attnfuse_bwd(const void* Q, const void* K, const void* V, const void* O, con
                   stream);
 }
 
+int af_bwd_blocksparse(const void* Q, const void* K, const void* V, const void* O, const void* dO,
+                       const float* LSE, void* dQ, void* dK, void* dV,
+                       const int* q_block_ptr, const int* k_block_idx,
+                       const int* k_block_ptr, const int* q_block_idx, int longest_list, long long list_tiles,
+                       void* workspace, size_t workspace_bytes,
+                       int B, int H, int H_kv, int S, int D, int dtype,
+                       int rope, float rope_theta, const float* rope_table, int rope_table_rows,
+                       int mask, int window,
+                       const float* alibi_slopes, float softmax_scale, void* stream) {
+  const int* m[] = {q_block_ptr, k_block_idx, k_block_ptr, q_block_idx};
+  for (const int* x : m) if (!x || !aligned4(x)) return AF_ERR_INVALID_ARG;
+  const void* outs[] = {dQ, dK, dV, workspace};
+  for (const void* x : outs)
+    for (const int* y : m) if (x == (const void*)y) return AF_ERR_INVALID_ARG;
+  if (S < 1 || S > kMaxSparseS) return AF_ERR_INVALID_ARG;
+  const Sparse sp{q_block_ptr, k_block_idx, k_block_ptr, q_block_idx, longest_list, list_tiles};
+  return bwd_impl(Q, K, V, O, dO, LSE, dQ, dK, dV, &sp, Ext{}, workspace, workspace_bytes, B, H, H_kv, S, D, dtype,
+                  rope, rope_theta, rope_table, rope_table_rows, mask, window, alibi_slopes, softmax_scale, stream);
+}
+
 int attnfuse_bwd_blocksparse(const void* Q, const void* K, const void* V, const void* O, const void* dO,
                              const float* LSE, void* dQ, void* dK, void* dV,
                              const int* q_block_ptr, const int* k_block_idx,
@@ -526,14 +587,14 @@ int attnfuse_bwd_blocksparse(const void* Q, const void* K, const void* V, const 
                              int rope, float rope_theta, const float* rope_table, int rope_table_rows,
                              int mask, int window,
                              const float* alibi_slopes, float softmax_scale, void* stream) {
-  const int* m[] = {q_block_ptr, k_block_idx, k_block_ptr, q_block_idx};
-  for (const int* x : m) if (!x || !aligned4(x)) return AF_ERR_INVALID_ARG;
-  const void* outs[] = {dQ, dK, dV, workspace};
-  for (const void* x : outs)
-    for (const int* y : m) if (x == (const void*)y) return AF_ERR_INVALID_ARG;
-  if (S < 1 || S > kMaxSparseS) return AF_ERR_INVALID_ARG;
-  return bwd_impl(Q, K, V, O, dO, LSE, dQ, dK, dV, m, Ext{}, workspace, workspace_bytes, B, H, H_kv, S, D, dtype,
-                  rope, rope_theta, rope_table, rope_table_rows, mask, window, alibi_slopes, softmax_scale, stream);
+  return af_bwd_blocksparse(Q, K, V, O, dO, LSE, dQ, dK, dV, q_block_ptr, k_block_idx, k_block_ptr, q_block_idx, 0, 0,
+                            workspace, workspace_bytes, B, H, H_kv, S, D, dtype, rope, rope_theta, rope_table,
+                            rope_table_rows, mask, window, alibi_slopes, softmax_scale, stream);
+}
+
+int af_bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window, int longest_list, long long list_tiles) {
+  const int w = window < S ? window : S, n = bwd_splits(B, H, H_kv, S, D, mask, w);
+  return list_tiles < 0 ? n : bwd_splits_sparse(B, H, H_kv, S, D, mask, w, longest_list, list_tiles, n);
 }
 
 int attnfuse_bwd_bias_norm(const void* Q, const void* K, const void* V, const void* O, const void* dO,

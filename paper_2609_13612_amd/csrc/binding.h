@@ -33,6 +33,23 @@ int af_fwd_ws(const void* Q, const void* K, const void* V, void* O, float* LSE, 
               int rope, float rope_theta, const float* rope_table, int rope_table_rows, int mask, int window,
               const float* alibi_slopes, float softmax_scale, void* stream);
 
+/* attnfuse_bwd_blocksparse, told how long the mask's lists are: the 64-row
+ * query tiles that the longest 128-key block of the mask (within the causal
+ * range under a causal or window mask) visits, and those of all of them.  0:
+ * not known, and one workgroup takes each key block. */
+int af_bwd_blocksparse(const void* Q, const void* K, const void* V, const void* O, const void* dO,
+                       const float* LSE, void* dQ, void* dK, void* dV,
+                       const int* q_block_ptr, const int* k_block_idx,
+                       const int* k_block_ptr, const int* q_block_idx, int longest_list, long long list_tiles,
+                       void* workspace, size_t workspace_bytes,
+                       int B, int H, int H_kv, int S, int D, int dtype,
+                       int rope, float rope_theta, const float* rope_table, int rope_table_rows,
+                       int mask, int window,
+                       const float* alibi_slopes, float softmax_scale, void* stream);
+
+/* Workgroups that share a key block in the bf16 dK/dV pass of these sizes; list_tiles < 0: without a block mask. */
+int af_bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window, int longest_list, long long list_tiles);
+
 #ifdef __cplusplus
 }
 #endif

@@ -285,7 +285,7 @@ PyObject* fwd(Args a) {
 }
 
 // bwd(q, k, v, o, do, lse, dq, dk, dv, workspace, slopes, table, tables, rope, theta, mask, window, scale,
-//     bias, sb, sh, sq, norm, q_block_ptr, k_block_idx, k_block_ptr, q_block_idx) -> (dQ, dK, dV)
+//     bias, sb, sh, sq, norm, q_block_ptr, k_block_idx, k_block_ptr, q_block_idx, longest, tiles) -> (dQ, dK, dV)
 PyObject* bwd(Args a) {
   Qkv x(a);
   const Tensor &o = a.need(), &dout = a.need();
@@ -299,6 +299,8 @@ PyObject* bwd(Args a) {
   const float scale = a.scale(x.D);
   const Bias bias(a);
   const int *qp = a.pointer<int>(), *ki = a.pointer<int>(), *kp = a.pointer<int>(), *qi = a.pointer<int>();
+  const int longest = a.size();
+  const long long tiles = a.whole();
   const Table tab = table_of(late, rope, theta, x.D, x.S, x.dev);
   const float* sl = slopes_of(slopes, x.H, x.dev);
   same(o, x.q.sizes(), x.type, x.dev);
@@ -320,9 +322,9 @@ PyObject* bwd(Args a) {
   const size_t n = (size_t)ws.numel() * ws.element_size();
   const int rc = enqueue(x.dev, [&](void* st) {
     if (qp)
-      return attnfuse_bwd_blocksparse(in(x.q), in(x.k), in(x.v), in(o), in(dout), lp, out(dq), out(dk),
-                                      out(dv), qp, ki, kp, qi, out(ws), n, B, H, Hkv, S, D, x.dtype, rope,
-                                      (float)theta, tab.ptr, tab.rows, mask, window, sl, scale, st);
+      return af_bwd_blocksparse(in(x.q), in(x.k), in(x.v), in(o), in(dout), lp, out(dq), out(dk), out(dv), qp, ki,
+                                kp, qi, longest, tiles, out(ws), n, B, H, Hkv, S, D, x.dtype, rope, (float)theta,
+                                tab.ptr, tab.rows, mask, window, sl, scale, st);
     return attnfuse_bwd_bias_norm(in(x.q), in(x.k), in(x.v), in(o), in(dout), lp, out(dq), out(dk),
                                   out(dv), bias.p, bias.sb, bias.sh, bias.sq, bias.norm, out(ws), n, B, H, Hkv, S,
                                   D, x.dtype, rope, (float)theta, tab.ptr, tab.rows, mask, window, sl, scale, st);

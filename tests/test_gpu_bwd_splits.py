@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from gpu_util import announce, assert_bf16_close, device_inputs, f64, need_gpu
-from paper_2609_13612_amd import api, inputs
+from paper_2609_13612_amd import _lib, api, blockmask, inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -46,5 +46,29 @@ def test_split_gradients(B, H, Hkv, S, D, rope, mask, window, norm):
     torch.cuda.synchronize()
     assert (ws[n:] == 0x5A).all(), "written past the workspace"
     ref = oracle.attention_backward(*[f64(cpu[x]) for x in ("q", "k", "v", "do")], **okw)
+    for name, a, r in zip(("dQ", "dK", "dV"), g, ref):
+        assert_bf16_close(a, r, name)
+
+
+@pytest.mark.parametrize("B,H,Hkv,S,D,rope,mask,window", [
+    (1, 8, 2, 1001, 64, "neox", "causal", None), (1, 16, 2, 700, 128, "none", "none", None),
+    (2, 8, 1, 650, 128, "interleaved", "sliding_window", 300)])
+def test_split_gradients_under_a_block_mask(B, H, Hkv, S, D, rope, mask, window):
+    """Lists of very different lengths (a global block, a band, an empty column): some shares hold nothing."""
+    need_gpu()
+    announce(f"bwd splits sparse {B} {H}/{Hkv} {S} {D} {rope} {mask}")
+    cpu, d = device_inputs(B, H, Hkv, S, D, seed=S, with_do=True)
+    nb = blockmask.num_blocks(S)
+    active = torch.from_numpy(inputs.bigbird_blocks(nb, n_random=1)).clone()
+    active[:, 3] = False
+    bm = blockmask.block_mask_from_dense(active.cuda(), S)
+    assert bm.col_tiles == blockmask.block_mask_from_dense(active, S).col_tiles
+    n = _lib.load().af_bwd_splits(B, H, Hkv, S, D, api.MASK[mask], window or 0, *bm.col_tiles[mask != "none"])
+    assert n > 1, "the case is meant to split"
+    kw = dict(rope=rope, mask=mask, window=window)
+    o, lse = api.attnfuse_fwd_blocksparse(d["q"], d["k"], d["v"], bm, **kw)
+    g = api.attnfuse_bwd_blocksparse(d["q"], d["k"], d["v"], o, d["do"], lse, bm, **kw)
+    ref = oracle.attention_backward(*[f64(cpu[x]) for x in ("q", "k", "v", "do")], theta=10000.0,
+                                    block_mask=bm.as_oracle(), **kw)
     for name, a, r in zip(("dQ", "dK", "dV"), g, ref):
         assert_bf16_close(a, r, name)
