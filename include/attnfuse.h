@@ -129,8 +129,8 @@ int attnfuse_fwd(const void* Q, const void* K, const void* V, void* O, float* LS
                  int mask, int window,
                  const float* alibi_slopes, float softmax_scale, void* stream);
 
-/* Bytes of device workspace attnfuse_bwd needs for these sizes and RoPE kind
- * (each part rounded up to a multiple of 256 bytes):
+/* Bytes of device workspace with which attnfuse_bwd of these sizes and RoPE kind
+ * runs fastest (each part rounded up to a multiple of 256 bytes):
  *   8*B*H*S                  per query row: the softmax backward's row term
  *                            delta_i and LSE_i in log2 units (fp32 each)
  * + 2*B*H*S*D                sigma * dO converted once to fp16
@@ -142,6 +142,10 @@ int attnfuse_fwd(const void* Q, const void* K, const void* V, void* O, float* LS
  * + 8*n*B*H_kv*S*D         where n > 1 workgroups share a key block in the dK/dV
  *                          pass (few K/V heads or short sequences; n <= 8):
  *                          their fp32 partial dK and dV
+ * The last part is not required: with less, down to nothing, as many workgroups
+ * (down to one) share a key block as their partials fit, and the sums of dK and
+ * dV are taken in that order.  So the total may fall as S grows, while a workspace
+ * sized for the longest S serves every shorter one.  AF_DTYPE_FP32 never uses it.
  * Returns 0 for invalid sizes. */
 size_t attnfuse_bwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int rope);
 
@@ -173,8 +177,9 @@ size_t attnfuse_bwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int ro
  *                        variant arguments (LSE must be the forward's)
  *   dQ [B,H,S,D], dK/dV [B,H_kv,S,D]  outputs (dtype), fully overwritten; must
  *                        not alias inputs
- *   workspace            device memory of >= attnfuse_bwd_workspace_bytes(B,
- *                        H, H_kv, S, D, rope) bytes (16-byte aligned),
+ *   workspace            device memory (16-byte aligned) of
+ *                        attnfuse_bwd_workspace_bytes(B, H, H_kv, S, D, rope)
+ *                        bytes, or fewer by what that says is not required;
  *                        caller-owned scratch, overwritten
  *   other arguments      as attnfuse_fwd.  AF_DTYPE_FP32 runs the fp32 debug
  *                        backward (same passes, fp32 arithmetic; it uses only

@@ -169,8 +169,8 @@ BwdWorkspace bwd_workspace(int B, int H, int H_kv, int S, int D, int rope) {
     w.qr16 = off; off += align256(rows * D * 2);
     w.kr16 = off; off += align256(krows * D * 2);
   }
-  // the size does not know the mask: room for the larger of the two that fix
-  // the split by the sizes alone (a window takes at most that)
+  // the reported size does not know the mask or the type: room for the larger of
+  // the two that fix the split by the sizes alone (a window takes at most that)
   w.splits = 1;
   if (supported_d(D)) {
     const int none = bwd_splits(B, H, H_kv, S, D, AF_MASK_NONE, 0), causal = bwd_splits(B, H, H_kv, S, D, AF_MASK_CAUSAL, 0);
@@ -180,6 +180,14 @@ BwdWorkspace bwd_workspace(int B, int H, int H_kv, int S, int D, int rope) {
   if (w.splits > 1) off += align256((size_t)w.splits * 2 * krows * D * sizeof(float));
   w.total = off;
   return w;
+}
+
+// The splits (at most n) whose partials a workspace of `bytes` holds.  Everything
+// before the partials is required; they are not, since the pass also runs unsplit: a
+// workspace sized for a longer sequence, which splits less, serves a shorter one.
+int splits_that_fit(int n, const BwdWorkspace& w, size_t bytes, size_t kv_elems) {
+  const size_t room = (bytes - w.part) / (kv_elems * 2 * sizeof(float));
+  return room < 2 ? 1 : room < (size_t)n ? (int)room : n;
 }
 
 // Decode workspace: per-wave partial (max, sum) pairs, then accumulators
@@ -304,7 +312,7 @@ int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const v
   if (rc != AF_OK) return rc;
   if ((rc = check_attn(mask, window, softmax_scale)) != AF_OK) return rc;
   if ((rc = check_table(rope, rope_table, rope_table_rows, S, outs, 4)) != AF_OK) return rc;
-  if (workspace_bytes < attnfuse_bwd_workspace_bytes(B, H, H_kv, S, D, rope)) return AF_ERR_INVALID_ARG;
+  if (workspace_bytes < bwd_workspace(B, H, H_kv, S, D, rope).part) return AF_ERR_INVALID_ARG;
   if (!supported_d(D)) return AF_ERR_UNSUPPORTED;
   if (sparse && dtype == AF_DTYPE_FP32) return AF_ERR_UNSUPPORTED;        // block-sparse: bf16 kernels only
   if (ext.kind() != af::EXT_NONE && (dtype == AF_DTYPE_FP32 || alibi_slopes || sparse)) return AF_ERR_UNSUPPORTED;
@@ -323,7 +331,7 @@ int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const v
   p.splits = 1;
   if (dtype == AF_DTYPE_BF16) {
     const int w = window < S ? window : S, dense = bwd_splits(B, H, H_kv, S, D, mask, w);
-    const int n = dense < ws.splits ? dense : ws.splits;
+    const int n = splits_that_fit(dense < ws.splits ? dense : ws.splits, ws, workspace_bytes, (size_t)B * H_kv * S * D);
     p.splits = sparse ? bwd_splits_sparse(B, H, H_kv, S, D, mask, w, sparse->longest, sparse->tiles, n) : n;
     p.part = reinterpret_cast<float*>(wb + ws.part);
   }
@@ -399,7 +407,7 @@ int af::fwd_waves(int B, int H, int Hkv, int S, int D, int rope, int mask, int w
 extern "C" {
 
 int attnfuse_version(void) { return kAbiVersion; }
-                     
+
 size_t attnfuse_rope_table_bytes(int rows, int D) {
   if (rows < 1 || rows > kMaxTableRows || D < 2 || (D & 1)) return 0;
   return table_bytes(rows, D);
@@ -592,8 +600,11 @@ int attnfuse_bwd_blocksparse(const void* Q, const void* K, const void* V, const 
                             rope_table_rows, mask, window, alibi_slopes, softmax_scale, stream);
 }
 
-int af_bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window, int longest_list, long long list_tiles) {
-  const int w = window < S ? window : S, n = bwd_splits(B, H, H_kv, S, D, mask, w);
+int af_bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window, int longest_list, long long list_tiles,
+                  size_t partial_bytes) {
+  const int w = window < S ? window : S;
+  BwdWorkspace ws{};
+  const int n = splits_that_fit(bwd_splits(B, H, H_kv, S, D, mask, w), ws, partial_bytes, (size_t)B * H_kv * S * D);
   return list_tiles < 0 ? n : bwd_splits_sparse(B, H, H_kv, S, D, mask, w, longest_list, list_tiles, n);
 }
 

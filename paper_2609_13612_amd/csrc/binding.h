@@ -47,8 +47,10 @@ int af_bwd_blocksparse(const void* Q, const void* K, const void* V, const void* 
                        int mask, int window,
                        const float* alibi_slopes, float softmax_scale, void* stream);
 
-/* Workgroups that share a key block in the bf16 dK/dV pass of these sizes; list_tiles < 0: without a block mask. */
-int af_bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window, int longest_list, long long list_tiles);
+/* Workgroups that share a key block in the bf16 dK/dV pass of these sizes, given
+ * partial_bytes of workspace for their partials; list_tiles < 0: without a block mask. */
+int af_bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window, int longest_list, long long list_tiles,
+                  size_t partial_bytes);
 
 #ifdef __cplusplus
 }

@@ -8,14 +8,17 @@ import torch
 from paper_2609_13612_amd import _lib, blockmask, inputs
 
 
-def _dense(B, H, Hkv, S, D, mask):
-    return _lib.load().af_bwd_splits(B, H, Hkv, S, D, mask, 0, 0, -1)
+ROOM = 1 << 40   # any number of partials fits
+
+
+def _dense(B, H, Hkv, S, D, mask, room=ROOM):
+    return _lib.load().af_bwd_splits(B, H, Hkv, S, D, mask, 0, 0, -1, room)
 
 
 def _sparse(B, H, Hkv, S, D, mask, active, window=0):
     bm = blockmask.block_mask_from_dense(torch.from_numpy(np.array(active)), S)
     longest, tiles = bm.col_tiles[mask != 0]
-    return _lib.load().af_bwd_splits(B, H, Hkv, S, D, mask, window, longest, tiles)
+    return _lib.load().af_bwd_splits(B, H, Hkv, S, D, mask, window, longest, tiles, ROOM)
 
 
 def _mask(kind, nb):
@@ -47,13 +50,13 @@ def test_all_active_is_the_dense_call(S, mask, window):
     lib = _lib.load()
     for B, H, Hkv in ((1, 8, 2), (1, 1, 1), (3, 16, 16)):
         for D in (64, 128):
-            want = lib.af_bwd_splits(B, H, Hkv, S, D, mask, window, 0, -1)
+            want = lib.af_bwd_splits(B, H, Hkv, S, D, mask, window, 0, -1, ROOM)
             assert _sparse(B, H, Hkv, S, D, mask, _mask("all", blockmask.num_blocks(S)), window) == want
 
 
 def test_unknown_lists_are_not_split():
     assert _dense(1, 32, 8, 2048, 128, 1) > 1
-    assert _lib.load().af_bwd_splits(1, 32, 8, 2048, 128, 1, 0, 0, 0) == 1
+    assert _lib.load().af_bwd_splits(1, 32, 8, 2048, 128, 1, 0, 0, 0, ROOM) == 1
 
 
 @pytest.mark.parametrize("S,density", [(64, 1.0), (65, 0.5), (600, 0.3), (1000, 0.0), (2111, 0.1)])
@@ -65,3 +68,38 @@ def test_list_lengths(S, density):
         n = [a[:, j:j + 2].any(axis=1).sum() for j in range(0, nb, 2)]
         assert got == (max(n), sum(n))
     assert bm.to("cpu").col_tiles == bm.col_tiles
+
+
+@pytest.mark.parametrize("B,H,Hkv,S,D,mask", [(1, 32, 8, 512, 128, 1), (1, 8, 2, 4000, 64, 1), (3, 16, 4, 1777, 128, 0)])
+def test_as_many_as_the_workspace_holds(B, H, Hkv, S, D, mask):
+    n, part = _dense(B, H, Hkv, S, D, mask), 8 * B * Hkv * S * D
+    assert n > 1
+    for room, want in ((0, 1), (part, 1), (2 * part - 1, 1), (2 * part, 2), (n * part - 1, n - 1), (n * part, n)):
+        assert _dense(B, H, Hkv, S, D, mask, room) == want
+
+
+def _unsplit_bytes(B, H, Hkv, S, D, rope):
+    """What the backward needs without partials, section by section."""
+    up = lambda x: (x + 255) & ~255
+    n = 2 * up(4 * B * H * S) + up(2 * B * H * S * D) + up(4 * B * Hkv)
+    n += up(4 * B * Hkv * -(-(H // Hkv) * S * D // 16384))
+    return n + (up(2 * B * H * S * D) + up(2 * B * Hkv * S * D) if rope else 0)
+
+
+@pytest.mark.parametrize("B,H,Hkv,S,D", [(1, 32, 8, 512, 128), (1, 8, 2, 4000, 64), (3, 16, 4, 1777, 128),
+                                         (1, 32, 8, 8192, 128)])
+@pytest.mark.parametrize("rope", [0, 1])
+def test_room_for_partials_is_not_required(B, H, Hkv, S, D, rope):
+    """A workspace without room for partials is accepted in both types: with it the call is refused later, for a bias
+    together with slopes (bf16) or a bias (fp32), and one byte less is an invalid argument."""
+    lib = _lib.load()
+    need = _unsplit_bytes(B, H, Hkv, S, D, rope)
+    assert need <= lib.attnfuse_bwd_workspace_bytes(B, H, Hkv, S, D, rope)
+    p = [0x1000000 * i for i in range(1, 14)]
+
+    def code(dtype, nbytes):
+        return lib.attnfuse_bwd_bias_norm(*p[:9], p[10], 0, 0, 0, 0, p[9], nbytes, B, H, Hkv, S, D, dtype, rope, 1e4,
+                                          p[11], S, 1, 0, p[12], 0.1, None)
+    for dtype in (0, 1):
+        assert code(dtype, need) == -2
+        assert code(dtype, need - 1) == -1

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import announce, assert_bf16_close, device_inputs, f64, need_gpu
+from gpu_util import announce, assert_bf16_close, assert_fp32_close, device_inputs, f64, need_gpu
 from paper_2609_13612_amd import _lib, api, blockmask, inputs
 
 pytestmark = pytest.mark.gpu
@@ -63,7 +63,7 @@ def test_split_gradients_under_a_block_mask(B, H, Hkv, S, D, rope, mask, window)
     active[:, 3] = False
     bm = blockmask.block_mask_from_dense(active.cuda(), S)
     assert bm.col_tiles == blockmask.block_mask_from_dense(active, S).col_tiles
-    n = _lib.load().af_bwd_splits(B, H, Hkv, S, D, api.MASK[mask], window or 0, *bm.col_tiles[mask != "none"])
+    n = _lib.load().af_bwd_splits(B, H, Hkv, S, D, api.MASK[mask], window or 0, *bm.col_tiles[mask != "none"], 1 << 40)
     assert n > 1, "the case is meant to split"
     kw = dict(rope=rope, mask=mask, window=window)
     o, lse = api.attnfuse_fwd_blocksparse(d["q"], d["k"], d["v"], bm, **kw)
@@ -72,3 +72,28 @@ def test_split_gradients_under_a_block_mask(B, H, Hkv, S, D, rope, mask, window)
                                     block_mask=bm.as_oracle(), **kw)
     for name, a, r in zip(("dQ", "dK", "dV"), g, ref):
         assert_bf16_close(a, r, name)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_smaller_workspaces(dtype):
+    """One workspace of the longest sequence's size serves shorter ones that would share more, one without room for any
+    partials works too, and neither is written past its end."""
+    need_gpu()
+    B, H, Hkv, D = 1, 8, 2, 64
+    size = lambda S: api.attnfuse_bwd_workspace_bytes(B, H, Hkv, S, D, "neox")
+    unsplit = lambda S: 2 * B * S * D * (2 * H + Hkv) + 8 * B * H * S + 4096   # (4096: the small sections, with slack)
+    room = lambda S, n: _lib.load().af_bwd_splits(B, H, Hkv, S, D, 1, 0, 0, -1, max(0, n - unsplit(S)))
+    longest = size(700)
+    assert room(1000, unsplit(1000)) == 1 < room(1000, unsplit(1000) + 3 * 8 * B * Hkv * 1000 * D) < room(1000, 1 << 40)
+    for S, n in ((700, longest), (300, longest), (1000, unsplit(1000)), (1000, unsplit(1000) + 3 * 8 * B * Hkv * 1000 * D)):
+        announce(f"bwd workspace {dtype} {S} {n}")
+        cpu, d = device_inputs(B, H, Hkv, S, D, dtype=dtype, seed=S, with_do=True)
+        o, lse = api.attnfuse_fwd(d["q"], d["k"], d["v"], rope="neox")
+        ws = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        g = api.attnfuse_bwd(d["q"], d["k"], d["v"], o, d["do"], lse, rope="neox", workspace=ws[:n])
+        torch.cuda.synchronize()
+        assert (ws[n:] == 0x5A).all(), "written past the workspace"
+        ref = oracle.attention_backward(*[f64(cpu[x]) for x in ("q", "k", "v", "do")], rope="neox", theta=10000.0,
+                                        mask="causal")
+        for name, a, r in zip(("dQ", "dK", "dV"), g, ref):
+            (assert_bf16_close if dtype == "bf16" else assert_fp32_close)(a, r, name)
