@@ -160,10 +160,15 @@ __device__ __forceinline__ void tile_commit(TileRegs<D, ROPE, NW>& R, uint16_t* 
 // 4 rows (the transpose read) both fall on distinct banks.  f touches only the
 // chunk bits that the k-step (rows) or the column tile (transposed) counts in,
 // so four (or two) lane offsets and immediates address every read.
+// (The copies write M0, so the compiler has to know, though it warns of any
+// clobber of a register that it hands out by itself.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void async_copy16(const void* sbase, uint32_t voff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds)
-               : "memory");   // (nothing else in these kernels uses M0)
+               : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // Every copy this wave issued has landed (the barrier after it says so for all waves).
 __device__ __forceinline__ void async_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

@@ -2,6 +2,7 @@
 switch, and its per-source code-generation options name real sources (CPU
 tests; nothing is compiled)."""
 import os
+import re
 
 from paper_2609_13612_amd import build
 
@@ -37,3 +38,16 @@ def test_packed_fp32_is_off_for_every_device_source(monkeypatch):
         assert has == src.endswith(".hip"), src
         for f in build.SOURCE_FLAGS.get(src, []):
             assert f in cmd, (src, f)
+
+
+def test_inline_asm_declares_m0():
+    """Every asm statement that writes M0 says so: the compiler may keep a value of its own there (indexed registers)."""
+    found = 0
+    for name in sorted(os.listdir(build.CSRC)):
+        with open(os.path.join(build.CSRC, name)) as f:
+            statements = re.findall(r"\basm\b[^;]*?\((.*?)\);", f.read(), re.S)
+        for s in statements:
+            if re.search(r"\bm0\s*,", s):
+                assert re.search(r':[^:]*"m0"[^:]*$', s), f"{name}: {s}"
+                found += 1
+    assert found
