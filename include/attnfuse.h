@@ -154,7 +154,7 @@ size_t attnfuse_bwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int ro
  * that finds the gradient's scale and rotates K, a dQ pass over key tiles and a
  * dK/dV pass over query tiles; probabilities are re-derived from the saved
  * LSE).  The dQ pass also forms the row statistics and leaves the rotated Q in
- * the workspace (the tiles of both passes are read many times, so rotating once
+ * the workspace (under a block mask the first pass does; the tiles of both passes are read many times, so rotating once
  * is cheaper than re-rotating per visit); the gradients leave through the
  * inverse rotation:
  * dQ = R^T dQ', dK = R^T dK'.  For grouped-query attention dK and dV sum over

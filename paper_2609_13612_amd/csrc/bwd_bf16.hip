@@ -5,15 +5,16 @@
 // writer.
 //   1. bwd_pre:   partial maxima of |dO| per (batch, K/V head), and with RoPE
 //                 K' = R K rotated once into the workspace (fp16): the later
-//                 kernels read every K' tile many times.
+//                 kernels read every K' tile many times.  Under a block mask
+//                 Q' = R Q too.
 //   2. bwd_dq:    one workgroup per 128 or 256 query rows (GQA heads packed, as
 //                 in the forward); it loops over visible key tiles:
 //                 dQ' += scale dS K',  dQ = R^T dQ'.  Before the loop it forms
 //                 what else the passes need of its rows from the registers that
 //                 hold them: sigma (the power of two that brings the group's
 //                 largest |dO| into [1, 2)), delta_i = rowsum(dO_i * O_i), and
-//                 for the dK/dV pass Q' = R Q and sigma dO in fp16 in the
-//                 workspace.  Since it forms P and dP for every visible key of
+//                 for the dK/dV pass sigma dO and (without a block mask)
+//                 Q' = R Q in fp16 in the workspace.  Since it forms P and dP for every visible key of
 //                 its rows, it also sums the softmax backward's row term
 //                 delta_i = sum_j P_ij dP_ij in fp32 (with P renormalised by
 //                 its own row sum) and leaves it, and the renormalised LSE.
@@ -60,13 +61,18 @@ namespace af {
 // (batch, K/V head)'s G query heads (contiguous in [B, H, S, D]), as bf16
 // magnitude bits: the bit patterns of non-negative bf16 values order like the
 // values, so the maximum is an integer maximum.  With RoPE the blocks after
-// them rotate the key rows, one thread per chunk pair c (dims 8c.. and
-// D/2 + 8c.., NeoX partners; interleaved pairs stay in-chunk).  One pass over
-// dO and K, bound by HBM.  The rest of a preprocessing pass (delta, sigma dO,
+// them rotate the key rows, and under a block mask the query rows, one thread per
+// chunk pair c (dims 8c.. and D/2 + 8c.., NeoX partners; interleaved pairs stay
+// in-chunk).  One pass over dO and K (and Q), bound by HBM.  The rest of a preprocessing pass (delta, sigma dO,
 // Q', sigma itself) happens in the dQ pass, which holds those rows anyway: as
 // passes of their own they moved 370 MB more at B1 H32/8 S8192 D128 and cost
 // 64 us of 2.56 ms, at B8 H16 S2048 D64 43 of 515, at B4 H12 S4096 D64
-// block-sparse 16 of 293.
+// block-sparse 16 of 293.  Q' alone is the exception under a block mask: there
+// few tiles follow a workgroup's rotation, 5 us of VALU work at D = 128 with
+// two waves per SIMD, nothing is in flight meanwhile (the tile list comes after),
+// and this pass has the CUs to spare.  Whole backward, rotated there / in the dQ pass,
+// us: B1 H8 S381 D128 10 % random 38 / 44, B1 H12/4 S5873 D128 band of three 106 / 114;
+// over 200 drawn masks 1.11 times faster at the median.
 template <int D, int ROPE>
 __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdParams p, int dmax_blocks) {
   if ((int)blockIdx.x < dmax_blocks) {
@@ -104,11 +110,13 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdParams p, int dmax_bloc
     constexpr int RPB = 256 / TPR;         // rows per block
     const int c = threadIdx.x % TPR;
     const int d0 = 8 * c, d1 = D / 2 + 8 * c;
-    const long long rows = (long long)p.B * p.Hkv * p.S;
-    const long long row = (long long)(blockIdx.x - dmax_blocks) * RPB + threadIdx.x / TPR;
-    if (row < rows) {
+    const long long krows = (long long)p.B * p.Hkv * p.S, rows = krows + (p.bq_ptr ? (long long)p.B * p.H * p.S : 0);
+    const long long at = (long long)(blockIdx.x - dmax_blocks) * RPB + threadIdx.x / TPR;
+    if (at < rows) {   // key rows, then query rows
+      const bool key = at < krows;
+      const long long row = key ? at : at - krows;
       const int pos = (int)(row % p.S);
-      const uint16_t* Kr = static_cast<const uint16_t*>(p.k) + row * D;
+      const uint16_t* Kr = static_cast<const uint16_t*>(key ? p.k : p.q) + row * D;
       u32x4 k0 = ld16(Kr + d0), k1 = ld16(Kr + d1);
       if constexpr (ROPE == ROPE_NEOX) {
         rotate_neox8<false, true>(k0, k1, p.table + (size_t)pos * (D / 2) + 8 * c);
@@ -116,7 +124,7 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdParams p, int dmax_bloc
         rotate_interleaved8<false, true>(k0, p.table + (size_t)pos * (D / 2) + 4 * c);
         rotate_interleaved8<false, true>(k1, p.table + (size_t)pos * (D / 2) + D / 4 + 4 * c);
       }
-      uint16_t* kd = static_cast<uint16_t*>(p.kr16) + row * D;
+      uint16_t* kd = static_cast<uint16_t*>(key ? p.kr16 : p.qr16) + row * D;
       st16(kd + d0, k0);
       st16(kd + d1, k1);
     }
@@ -129,12 +137,11 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdParams p, int dmax_bloc
 // group's dO is all zero or holds an inf / NaN.
 __device__ __forceinline__ float group_scale(const BwdParams& p, int bg, int lane) {
   static_assert(DMAX_PARTS == 4 * 64, "four partial maxima per lane");
-  uint32_t mx = 0;
+  uint32_t part[4], mx = 0;   // (clamped rather than guarded: a guarded load waits for the one before it)
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = lane + 64 * j;
-    if (c < p.dmax_chunks) mx = max(mx, p.dmax[(long long)bg * p.dmax_chunks + c]);
-  }
+  for (int j = 0; j < 4; ++j) part[j] = p.dmax[(long long)bg * p.dmax_chunks + min(lane + 64 * j, p.dmax_chunks - 1)];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) mx = max(mx, part[j]);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
   const int E = (int)(mx >> 7);   // bf16 biased exponent (the sign bit is clear)
@@ -238,7 +245,8 @@ void bwd_dq_kernel(BwdParams p) {
   const int p_end = min(p0 + P, S);
   const size_t bh = (size_t)b * p.H + h;
 
-  const uint16_t* Qh = static_cast<const uint16_t*>(p.q) + bh * S * D;
+  constexpr bool QROT = ROT && !SPARSE;      // this pass rotates its query rows (under a block mask the first one did)
+  const uint16_t* Qh = static_cast<const uint16_t*>(ROT && SPARSE ? p.qr16 : p.q) + bh * S * D;
   const uint16_t* dOh = static_cast<const uint16_t*>(p.dout) + bh * S * D;
   const uint16_t* Kg = static_cast<const uint16_t*>(ROT ? p.kr16 : p.k) + (size_t)bg * S * D;
   const uint16_t* Vg = static_cast<const uint16_t*>(p.v) + (size_t)bg * S * D;
@@ -258,25 +266,27 @@ void bwd_dq_kernel(BwdParams p) {
 
   u32x4 qreg[C::KS], oreg[C::KS];
   const int mc = min(m, S - 1);   // rows past S compute on row S-1 and are never stored
-  const float sig = group_scale(p, bg, lane);
-  if (tid == 0 && hg == 0 && p0 == 0) p.dscale[bg] = sig;   // for the dK/dV pass
-  load_row_operand<D, ROPE, !ROT>(qreg, Qh, p.table, mc, S, lg);   // Q' (fp16)
   load_row_operand<D, ROPE_NONE>(oreg, dOh, nullptr, mc, S, lg);   // dO as it is
-  // sigma delta_i from rowsum(dO o O), and LSE_i in log2 units (+inf for an
-  // empty row, so its P is 0); relu attention has neither
+  // delta_i from rowsum(dO o O), and LSE_i in log2 units (+inf for an empty row,
+  // so its P is 0); relu attention has neither.  O's chunks are all in flight at
+  // once, and gone before the rotation needs registers
   float lse2 = INFINITY, del = 0.f;
   if constexpr (!RELU) {
     const uint16_t* Oh = static_cast<const uint16_t*>(p.o) + bh * S * D + (size_t)mc * D + 8 * lg;
+    u32x4 o[C::KS];
 #pragma unroll
-    for (int s = 0; s < C::KS; ++s) {
-      const u32x4 o = ld16(Oh + 16 * s);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) del += bf_lo(oreg[s][w]) * bf_lo(o[w]) + bf_hi(oreg[s][w]) * bf_hi(o[w]);
-    }
-    del = (m < S) ? pair_sum(del) * sig : 0.f;
+    for (int s = 0; s < C::KS; ++s) o[s] = ld16(Oh + 16 * s);
     const float l = p.lse[bh * S + mc];
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) del += bf_lo(oreg[s][w]) * bf_lo(o[s][w]) + bf_hi(oreg[s][w]) * bf_hi(o[s][w]);
     lse2 = (m < S && l != -INFINITY) ? l * kLog2e : INFINITY;
   }
+  const float sig = group_scale(p, bg, lane);
+  if (tid == 0 && hg == 0 && p0 == 0) p.dscale[bg] = sig;   // for the dK/dV pass
+  if constexpr (!RELU) del = pair_sum(del) * sig;
+  load_row_operand<D, QROT ? ROPE : ROPE_NONE, !ROT>(qreg, Qh, p.table, mc, S, lg);   // Q' (fp16)
   // the dK/dV pass's operands of these rows: sigma dO, and Q' under RoPE
   if (m < S) {
     const size_t row = (bh * S + m) * D + 8 * lg;
@@ -288,7 +298,7 @@ void bwd_dq_kernel(BwdParams p) {
       for (int w = 0; w < 4; ++w) x[w] = pack_f16(bf_lo(oreg[s][w]) * sig, bf_hi(oreg[s][w]) * sig);
       st16(od + 16 * s, x);
     }
-    if constexpr (ROT) {
+    if constexpr (QROT) {
       uint16_t* qd = static_cast<uint16_t*>(p.qr16) + row;
 #pragma unroll
       for (int s = 0; s < C::KS; ++s) st16(qd + 16 * s, qreg[s]);
@@ -463,8 +473,8 @@ struct BwdPasses {
   template <int D, int ROPE, int MASK, bool ALIBI, int EXT>
   static int run(const BwdParams& p, hipStream_t st) {
     constexpr int RPB = 256 / (D / 16);
-    const long long krows = (ROPE != ROPE_NONE) ? (long long)p.B * p.Hkv * p.S : 0;
-    const int k_blocks = (int)((krows + RPB - 1) / RPB);
+    const long long rows = (ROPE != ROPE_NONE) ? (long long)p.B * (p.Hkv + (p.bq_ptr ? p.H : 0)) * p.S : 0;
+    const int k_blocks = (int)((rows + RPB - 1) / RPB);
     const int d_blocks = p.B * p.Hkv * p.dmax_chunks;
     hipLaunchKernelGGL((bwd_pre_kernel<D, ROPE>), dim3((unsigned)(d_blocks + k_blocks)), dim3(256), 0, st, p, d_blocks);
     const int nw = (EXT == EXT_NONE && p.bq_ptr) ? dq_waves(ROPE, true) : dq_waves(ROPE, false);

@@ -235,3 +235,18 @@ def test_blocksparse_noncanonical_lists():
     grads, ref = _bwd_given_o(cpu, dev, bm, "neox", "causal", None, None)
     for name, g, r in zip(("dQ", "dK", "dV"), grads, ref):
         assert_bf16_close(g, r, name)
+
+
+@pytest.mark.parametrize("B,H,Hkv,S,D,rope", [(2, 6, 2, 1, 128, "neox"), (1, 3, 3, 33, 64, "interleaved"),
+                                              (2, 4, 4, 129, 128, "interleaved"), (3, 5, 1, 191, 64, "neox")])
+def test_blocksparse_gradients_with_rope_at_ragged_sizes(B, H, Hkv, S, D, rope):
+    """Row counts that do not fill the workgroups that rotate keys and queries in one launch."""
+    need_gpu()
+    announce(f"blocksparse rope rows {B} {H}/{Hkv} {S} {D} {rope}")
+    cpu, dev = device_inputs(B, H, Hkv, S, D, seed=S, with_do=True)
+    nb = blockmask.num_blocks(S)
+    active = torch.from_numpy(inputs.random_blocks(nb, 0.7, seed=2)) | torch.eye(nb, dtype=torch.bool)
+    bm = blockmask.block_mask_from_dense(active, S, device="cuda")
+    g, ref = _bwd_given_o(cpu, dev, bm, rope, "causal", None, None)
+    for name, a, r in zip(("dQ", "dK", "dV"), g, ref):
+        assert_bf16_close(a, r, name)
