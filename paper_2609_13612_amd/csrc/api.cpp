@@ -478,6 +478,13 @@ int attnfuse_fwd_bias_norm(const void* Q, const void* K, const void* V, void* O,
 //   D = 64, H12 B4 causal, S 512 / 1024 / 2048 / 4096: 13.4 / 15.7, 23.4 / 24.5, 48.5 / 49.5, 160 / 136; no mask 2048:
 //   89.6 / 73.5; window 256 at 4096: 58.5 / 47.1; B32 H16 S512: 58.5 / 55.2;
 //   block-sparse (9.2 % active) B4 H12 S4096 D64: 123 / 82; relu attention gains the rotation alone.
+// Under a block mask the saving is the tiles' of an average workgroup while all
+// run at once, then a part per workgroup that a CU takes in turn and per tile
+// (fitted to 3000 drawn masks; a D = 64 mask without a causal range may hold a row
+// far longer than the average, which hides that part in few turns).  With 0.6 us for
+// every tile of all forms, as first, 30 of 222 calls that took it were slower by up to
+// 25 % (B2 H32/8 S6316 D128 30 % random, window 25 72.5 / 86.8, B3 H8/2 S4910 D64 10 %
+// random causal 27.9 / 31.3); now 3 of 174 by 3 to 5 %.
 // An estimate in terms of 256-row workgroups, whichever form then runs: the
 // saving follows the tiles of the longest workgroup while these leave CUs free,
 // and otherwise the workgroups each CU takes in turn (5 us each) and the tiles of
@@ -498,7 +505,13 @@ size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, i
   const double nt = (S + 63) / 64;
   double saved;
   if (sparse_blocks) {
-    saved = 0.6 * units * (double)sparse_blocks * (mask == AF_MASK_NONE ? 1.0 : 0.5) / 256.0;
+    // tiles visited, were the mask even: half of them under a causal mask, those of the band under a window
+    double tiles = (double)sparse_blocks * (mask == AF_MASK_NONE ? 1.0 : 0.5);
+    if (mask == AF_MASK_SLIDING_WINDOW) tiles = std::fmin(tiles, (double)sparse_blocks * std::fmin(1.0, (window / 64.0 + 1.5) / nt));
+    const double turns = units * nt / 256.0, load = units * tiles / 256.0;
+    if (turns <= 1.0) saved = 0.3 + (D == 128 ? 0.5 : 0.25) * tiles / nt;
+    else if (D == 128) saved = 0.25 * (turns - 1.0) + 0.37 * load;
+    else saved = (mask == AF_MASK_NONE ? 2.0 * (turns - 3.0) : (hp == 1 ? 1.5 : 1.0) * turns - 0.7) + 0.22 * load;
   } else {
     const double rows = 256.0 / hp, wgs = std::ceil(S / rows);
     double longest = nt, tiles = wgs * nt;   // key tiles of the longest workgroup, and of all of a unit's
