@@ -144,3 +144,36 @@ def test_gradients_through_saved_tensor_hooks():
         o = autograd.attention(*leaves, rope="neox")
     got = torch.autograd.grad(o, leaves, d["do"])
     assert all(torch.equal(x, y) for x, y in zip(want, got))
+
+
+def test_same_bits_where_the_forward_takes_scratch(monkeypatch):
+    """The calls with the longest argument list (scratch, a bias's strides, a block mask's lists), each against the Python
+    marshalling and against the keys rotated in the loop."""
+    need_gpu()
+    announce("native against python marshalling, with scratch")
+    B, H, HKV, S, D = 2, 16, 4, 2048, 128
+    _, d = device_inputs(B, H, HKV, S, D, seed=6)
+    q, k, v = d["q"], d["k"], d["v"]
+    nb = blockmask.num_blocks(S)
+    bm = blockmask.block_mask_from_dense(inputs.random_blocks(nb, 0.9, seed=1), S, "cuda")
+    g = torch.Generator("cuda").manual_seed(1)
+    biases = [torch.randn(s, generator=g, device="cuda") for s in ((B, 1, 1, S), (1, H, 1, S), (1, 1, S, S))]
+    slopes = inputs.alibi_slopes(H).cuda()
+    norms = [(n, b) for n in ("softmax", "relu") for b in [None] + biases]
+    for rope, mask, window in (("neox", "causal", None), ("interleaved", "none", None), ("neox", "sliding_window", 1500)):
+        kw = dict(rope=rope, theta=500000.0, mask=mask, window=window)
+        calls = [(0, 0, lambda s=s: api.attnfuse_fwd(q, k, v, alibi_slopes=s, **kw)) for s in (None, slopes)]
+        calls += [(0, bm.k_idx.numel(), lambda s=s: api.attnfuse_fwd_blocksparse(q, k, v, bm, alibi_slopes=s, **kw))
+                  for s in (None, slopes)]
+        calls += [(api.NORM[n], 0, lambda n=n, b=b: api.attnfuse_fwd_bias_norm(q, k, v, norm=n, bias=b, **kw))
+                  for n, b in norms]
+        for norm, blocks, call in calls:
+            assert api._fwd_scratch_bytes(B, H, HKV, S, D, 0, api.ROPE[rope], api.MASK[mask], window or 0, norm, blocks) > 0
+            a = call()
+            with monkeypatch.context() as m:
+                m.setattr(api, "_native", None)
+                b = call()
+                m.setattr(api, "_fwd_scratch", lambda *a, **kw: None)
+                c = call()
+            for x, y, z in zip(a, b, c):
+                assert (x is None and y is None and z is None) or (torch.equal(x, y) and torch.equal(x, z))
