@@ -45,6 +45,7 @@ BINDING_SIGNATURES = {
     "af_bwd_blocksparse": (_I, [_P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _I, _L, _P, ctypes.c_size_t,
                                 _I, _I, _I, _I, _I, _I, _I, _F, _P, _I, _I, _I, _P, _F, _P]),
     "af_bwd_splits": (_I, [_I, _I, _I, _I, _I, _I, _I, _I, _L, ctypes.c_size_t]),
+    "af_col_tiles": (None, [_P, _I, ctypes.POINTER(_L)]),
     "af_fwd_waves": (_I, [_I, _I, _I, _I, _I, _I, _I, _I, _I]),
     "af_fwd_ws": (_I, [_P, _P, _P, _P, _P, _P, _P, _P, _L, _L, _L, _I, _P, ctypes.c_size_t,
                        _I, _I, _I, _I, _I, _I, _I, _F, _P, _I, _I, _I, _P, _F, _P]),

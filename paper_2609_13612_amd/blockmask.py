@@ -9,10 +9,13 @@ used by the forward and the dQ pass) and by key block (CSC: ``k_ptr`` /
 on the mask's device) set-up, done once per mask; no attention arithmetic
 happens here.
 """
+import ctypes
 from dataclasses import dataclass
 
 import numpy as np
 import torch
+
+from . import _lib
 
 BLOCK = 64
 MAX_BLOCKS = 2048          # per side; S <= 64 * 2048
@@ -72,13 +75,10 @@ def _compress(active):
 
 def _col_tiles(active):
     """BlockMask.col_tiles of a bool matrix."""
-    res = []
-    for a in (active, active.tril()):
-        a = torch.nn.functional.pad(a, (0, a.shape[1] % 2))
-        n = (a[:, 0::2] | a[:, 1::2]).sum(dim=0)
-        res += [n.max(), n.sum()]
-    longest, tiles, longest_lower, tiles_lower = torch.stack(res).tolist()
-    return (longest, tiles), (longest_lower, tiles_lower)
+    a = active.cpu().contiguous()
+    out = (ctypes.c_longlong * 4)()
+    _lib.load().af_col_tiles(a.data_ptr(), a.shape[0], out)
+    return (out[0], out[1]), (out[2], out[3])
 
 
 def block_mask_from_dense(active, S, device=None):

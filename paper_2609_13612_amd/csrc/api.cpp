@@ -613,6 +613,28 @@ int attnfuse_bwd_blocksparse(const void* Q, const void* K, const void* V, const 
                             rope_table_rows, mask, window, alibi_slopes, softmax_scale, stream);
 }
 
+void af_col_tiles(const unsigned char* active, int nb, long long* lengths) {
+  long long longest[2] = {0, 0}, all[2] = {0, 0};
+  for (int j0 = 0; j0 < nb; j0 += 64) {   // 64 columns (32 pairs) of every row at a time
+    const int j1 = j0 + 64 < nb ? j0 + 64 : nb;
+    long long n[2][32] = {};
+    for (int i = 0; i < nb; ++i) {
+      const unsigned char* row = active + (size_t)i * nb;
+      for (int j = j0; j < j1; j += 2) {
+        const int a = row[j], b = j + 1 < nb ? row[j + 1] : 0, p = (j - j0) / 2;
+        n[0][p] += a | b;
+        n[1][p] += (j <= i ? a : 0) | (j + 1 <= i ? b : 0);
+      }
+    }
+    for (int m = 0; m < 2; ++m)
+      for (long long x : n[m]) {
+        all[m] += x;
+        if (x > longest[m]) longest[m] = x;
+      }
+  }
+  for (int m = 0; m < 2; ++m) { lengths[2 * m] = longest[m]; lengths[2 * m + 1] = all[m]; }
+}
+
 int af_bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window, int longest_list, long long list_tiles,
                   size_t partial_bytes) {
   const int w = window < S ? window : S;

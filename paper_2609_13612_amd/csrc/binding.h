@@ -47,6 +47,11 @@ int af_bwd_blocksparse(const void* Q, const void* K, const void* V, const void* 
                        int mask, int window,
                        const float* alibi_slopes, float softmax_scale, void* stream);
 
+/* The list lengths af_bwd_blocksparse takes, of a block mask [nb][nb] in host
+ * memory (a byte per block, 0 or 1): {longest, all} without an elementwise mask,
+ * then within the causal range. */
+void af_col_tiles(const unsigned char* active, int nb, long long* lengths);
+
 /* Workgroups that share a key block in the bf16 dK/dV pass of these sizes, given
  * partial_bytes of workspace for their partials; list_tiles < 0: without a block mask. */
 int af_bwd_splits(int B, int H, int H_kv, int S, int D, int mask, int window, int longest_list, long long list_tiles,
