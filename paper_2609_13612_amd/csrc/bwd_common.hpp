@@ -81,18 +81,9 @@ __device__ __forceinline__ void store_grad_rows(f32x16 (&acc)[D / 32], float sca
   store_rows_bf16<D>(acc, lds, dst + (size_t)n0 * D, S - n0, lane);
 }
 
-// Transposed MFMA A operand from a row-major LDS tile: rows (keys or queries)
-// base_row + {4 lg + i/4, +8} and 16 dims per 16-lane group (lds_read_tr16).
-__device__ __forceinline__ u32x4 tr_operand(const uint16_t* tile, int pitch, int row0, int col0, int lane) {
-  const int lg = lane >> 5;
-  const uint16_t* p = tile + (row0 + 4 * lg + ((lane & 15) >> 2)) * pitch + col0 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const u32x2 lo = lds_read_tr16(p);
-  const u32x2 hi = lds_read_tr16(p + 8 * pitch);
-  return u32x4{lo[0], lo[1], hi[0], hi[1]};
-}
-
-// The same operand from a swizzled tile (swz_at): rows row0 + {4 lg + i/4, +8}
-// (row0 a multiple of 16), columns 32 mt + ..., through the lane's SwzLane.
+// Transposed MFMA A operand from a swizzled LDS tile (swz_at): rows (keys or
+// queries) row0 + {4 lg + i/4, +8} (row0 a multiple of 16), 16 dims per 16-lane
+// group (lds_read_tr16) from column 32 mt on, through the lane's SwzLane.
 template <int D>
 __device__ __forceinline__ u32x4 tr_operand_swz(const uint16_t* tile, const SwzLane<D>& z, int row0, int mt) {
   const uint16_t* t = tile + row0 * D;

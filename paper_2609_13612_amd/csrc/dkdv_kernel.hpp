@@ -107,10 +107,13 @@ __device__ __forceinline__ void qtile_commit(const QTileRegs<D, BQ>& R, uint16_t
 // The block's K' rows (B operand of S = Q' K'^T) and V rows (fp16, B operand
 // of dP = dO V^T) stay resident in LDS, leaving the registers to the dK/dV
 // accumulators.  Copying the query tiles straight to LDS frees 14 registers
-// and the LDS writes; the pass is bound by its operand reads and the barrier
-// that keeps its waves in step, so it gains 2 % where every CU has a workgroup
-// (B1 H32/8 S8192 D128 causal 1159 -> 1136 us) and 12 % where some have none
-// (B3 H16/4 S1777, 168 workgroups: 251 -> 221).
+// and the LDS writes; it gains 2 % where every CU has a workgroup (B1 H32/8
+// S8192 D128 causal 1159 -> 1136 us) and 12 % where some have none (B3 H16/4
+// S1777, 168 workgroups: 251 -> 221).  The next tile does not fly during a step as
+// the source suggests: qstat_load uses the statistics that it loads after the
+// tile's copies, loads return in order, so the compiled step waits for the whole
+// tile before its first MFMA (with ALiBi again for the slope, with a bias for the
+// bias).  What that wait costs has not been measured.
 template <int D, int ROPE, int MASK, bool ALIBI, bool SPARSE, int EXT, bool SPLIT>
 __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdParams p) {
   // at D = 64 a 128-row query tile halves the steps (barriers, staging) per
