@@ -381,9 +381,11 @@ int heads_packed(int G, int max) {
 // 350 the interleaved form at D = 128 lost 1 to 9 %, its four-wave kernel spills).
 // In more than a round they lose 10 to 28 % without a mask (B6 H16/2 S400 D128
 // 29.9 and 38.0, B3 H12 S1000 D64 30.4 and 34.4), and win only
+//   where all of them are resident, two to a CU, while eight waves need a second round (B6 H16 S616 D64 22.6 and 35.3);
 //   with a causal mask at D = 64 (4 to 14 %) or, NeoX, over 128 to 256 rows (0 to 9 %);
-//   under a window whose edges the finer rows cut: 8 to 50 % where a workgroup visits at most three quarters of the
-//   tiles (window 100, one head per workgroup), otherwise they lose up to 14 %.
+//   under a window, whose edges the finer rows cut, by up to 60 % (B6 H16 S604 D64 window 66 15.2 and 24.6, B6 H24/8
+//   S423 D128 window 23 26.5 and 40.0), but for packed heads of longer rows in one to two rounds (B3 H32/8 S512 D128
+//   window 100 23.0 and 20.1).  There the keys that a workgroup visits stand in for the row's length.
 int af::fwd_waves(int B, int H, int Hkv, int S, int D, int rope, int mask, int window, int bias) {
   const int G = H / Hkv, rows4 = 128 / heads_packed(G, 4), rows8 = 256 / heads_packed(G, 8);
   const bool cut = mask == AF_MASK_SLIDING_WINDOW;
@@ -395,13 +397,12 @@ int af::fwd_waves(int B, int H, int Hkv, int S, int D, int rope, int mask, int w
     if (bias == 1 && mask == AF_MASK_CAUSAL && n8 >= 512 && S >= 2048) return 8;
     return S < 6144 ? 4 : 8;
   }
-  if (S > (D == 64 ? 1024 : rope == AF_ROPE_INTERLEAVED && !cut ? 256 : 512)) return 8;
-  if (n4 <= 256) return 4;
+  const int keys = cut && window < S - rows8 ? rows8 + window : S;   // that a workgroup visits
+  if (keys > (D == 64 ? 1024 : rope == AF_ROPE_INTERLEAVED && !cut ? 256 : 512)) return 8;
+  if (n4 <= 256 || n4 == n8 || (n8 > 256 && n4 <= 512)) return 4;
+  if (cut) return rows4 == 128 || n8 > 256 || S <= 256 || n4 <= 320 ? 4 : 8;
   if (n8 >= 256 || mask == AF_MASK_NONE) return 8;
-  if (!cut) return D == 64 || (rope == AF_ROPE_NEOX && S >= 128 && S <= 256 && rows4 < rows8) ? 4 : 8;
-  const double nt = (S + 63) / 64;
-  const auto tiles = [&](int rows) { return std::fmin(nt, (rows + (double)window) / 64.0 + 1.0); };
-  return tiles(rows4) <= 0.75 * tiles(rows8) ? 4 : 8;
+  return D == 64 || (rope == AF_ROPE_NEOX && S >= 128 && S <= 256 && rows4 < rows8) ? 4 : 8;
 }
 
 extern "C" {

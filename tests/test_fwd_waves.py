@@ -19,9 +19,14 @@ def _waves(B, H, Hkv, S, D, rope, mask, window=0, bias=0):
     # more than a round without a mask: lost 10 to 28 %
     ((6, 16, 2, 400, 128, NEOX, NONE), 8), ((10, 8, 8, 512, 128, INTER, NONE), 8), ((3, 12, 12, 1000, 64, NEOX, NONE), 8),
     ((6, 40, 8, 176, 128, NEOX, NONE), 8), ((3, 12, 12, 919, 64, INTER, NONE), 8),
-    # and with one: won at D = 64, and under a window that the finer rows cut
+    # and with one: won at D = 64, and under most windows
     ((3, 12, 12, 1000, 64, NEOX, CAUSAL), 4), ((6, 32, 8, 270, 128, INTER, CAUSAL), 8), ((3, 12, 12, 1000, 64, NEOX, WINDOW, 100), 4),
-    ((10, 8, 2, 1000, 64, NEOX, WINDOW, 100), 8), ((3, 32, 8, 512, 128, NEOX, WINDOW, 100), 8),
+    ((10, 8, 2, 1000, 64, NEOX, WINDOW, 100), 4), ((3, 32, 8, 512, 128, NEOX, WINDOW, 100), 8),   # 20.7 / 23.6, 23.0 / 20.1
+    # 17.0 / 22.5, 18.3 / 20.3, 15.4 / 24.5, 25.7 / 39.3, 9.1 / 10.4
+    ((4, 12, 12, 790, 64, NEOX, WINDOW, 337), 4), ((4, 12, 12, 1024, 64, NEOX, WINDOW, 256), 4), ((6, 16, 16, 604, 64, NEOX, WINDOW, 66), 4),
+    ((6, 24, 8, 423, 128, NEOX, WINDOW, 23), 4), ((8, 8, 2, 534, 64, NEOX, WINDOW, 29), 4),
+    # all four-wave workgroups resident, eight waves in two rounds, or the same number of either: 23.1 / 35.7, 9.2 / 15.0
+    ((6, 16, 16, 616, 64, NEOX, NONE), 4), ((8, 40, 8, 35, 128, INTER, WINDOW, 32), 4),
     # the interleaved four-wave kernel spills at D = 128
     ((1, 32, 8, 512, 128, INTER, CAUSAL), 8), ((1, 32, 8, 512, 128, INTER, WINDOW, 100), 4),
     ((1, 32, 8, 600, 128, NEOX, CAUSAL), 8), ((1, 12, 12, 1100, 64, NEOX, CAUSAL), 8),
