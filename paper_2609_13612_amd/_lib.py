@@ -41,7 +41,7 @@ SIGNATURES = {
 
 # Symbols of csrc/binding.h, which only this package calls.
 BINDING_SIGNATURES = {
-    "af_fwd_workspace_bytes": (ctypes.c_size_t, [_I, _I, _I, _I, _I, _I, _I, _I, _I, _I, _L]),
+    "af_fwd_workspace_bytes": (ctypes.c_size_t, [_I, _I, _I, _I, _I, _I, _I, _I, _I, _I, _I, _L]),
     "af_bwd_blocksparse": (_I, [_P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _I, _L, _P, ctypes.c_size_t,
                                 _I, _I, _I, _I, _I, _I, _I, _F, _P, _I, _I, _I, _P, _F, _P]),
     "af_bwd_splits": (_I, [_I, _I, _I, _I, _I, _I, _I, _I, _L, ctypes.c_size_t]),

@@ -198,11 +198,11 @@ def _fwd_scratch_bytes(*sizes):
     return _lib.load().af_fwd_workspace_bytes(*sizes)
 
 
-def _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, blocks=0, norm=0):
+def _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, blocks=0, norm=0, extra=0):
     """Scratch for keys rotated once ahead of a forward, where that is faster
     (af_fwd_workspace_bytes), else None.  Without memory for it the keys are
     rotated in the loop: the same result."""
-    n = _fwd_scratch_bytes(B, H, Hkv, S, D, DTYPE[q.dtype], r, m, w, norm, blocks) if r else 0
+    n = _fwd_scratch_bytes(B, H, Hkv, S, D, DTYPE[q.dtype], r, m, w, norm, extra, blocks) if r else 0
     if n == 0:
         return None
     try:
@@ -227,7 +227,7 @@ def attnfuse_fwd(q, k, v, *, rope="none", theta=10000.0, mask="causal", window=N
     r, th, m, w, sc = _variant(rope, theta, mask, window, alibi_slopes, scale, D, H, dev)
     tab = _table(rope, theta, D, S, dev, rope_table)
     tp, tr = _tab(tab)
-    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w)
+    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, extra=int(alibi_slopes is not None))
     with torch.cuda.device(dev):
         if ws is not None:
             code = _lib.load().af_fwd_ws(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), None, None, None, 0, 0, 0, 0,
@@ -305,7 +305,7 @@ def attnfuse_fwd_blocksparse(q, k, v, block_mask, *, rope="none", theta=10000.0,
     r, th, m, w, sc = _variant(rope, theta, mask, window, alibi_slopes, scale, D, H, dev)
     tab = _table(rope, theta, D, S, dev, rope_table)
     tp, tr = _tab(tab)
-    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, blocks)
+    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, blocks, extra=int(alibi_slopes is not None))
     with torch.cuda.device(dev):
         if ws is not None:
             code = _lib.load().af_fwd_ws(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), qp, ki, None, 0, 0, 0, 0,
@@ -387,7 +387,7 @@ def attnfuse_fwd_bias_norm(q, k, v, *, bias=None, norm="softmax", rope="none", t
     r, th, m, w, sc = _variant(rope, theta, mask, window, None, scale, D)
     tab = _table(rope, theta, D, S, dev, rope_table)
     tp, tr = _tab(tab)
-    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, norm=NORM[norm])
+    ws = _fwd_scratch(q, B, H, Hkv, S, D, r, m, w, norm=NORM[norm], extra=int(bias is not None))
     with torch.cuda.device(dev):
         if ws is not None:
             code = _lib.load().af_fwd_ws(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), None, None, bp, sb, sh, sq,

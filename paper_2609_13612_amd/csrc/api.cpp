@@ -374,7 +374,8 @@ int heads_packed(int G, int max) {
 // finish no sooner, all being equal without a mask: D = 64 B1 H12 S4096 76.1 with
 // four, 73.3 with eight (staged through registers; 96.3 and 91.4 with a key bias),
 // D = 128 with a key bias, whose loads wait for the copies, B1 H16/4 S3000 97.3 and 85.8,
-// S2048 H32/8 77.0 and 71.9, causal S4096 159 and 145.  (With a bias row per query
+// S2048 H32/8 77.0 and 71.9, causal S4096 159 and 145 (but with one head a workgroup four
+// win: B3 H24/8 S4102 395 and 414).  (With a bias row per query
 // four win: D = 64 B2 H16 S2048 72.5 and 93.)  Rotating in the loop doubles that work
 // too.  There four waves win on short rows while their workgroups fit one round
 // of the CUs (8 to 40 % at S 64 to 512 with D = 128, to 1024 with D = 64; from S
@@ -394,13 +395,13 @@ int af::fwd_waves(int B, int H, int Hkv, int S, int D, int rope, int mask, int w
   if (rope == AF_ROPE_NONE) {   // copied to LDS
     if (D == 64) return mask == AF_MASK_NONE && bias < 2 && n4 > 256 && n4 <= 512 && S >= (bias ? 1024 : 2048) ? 8 : 4;
     if (bias == 1 && mask == AF_MASK_NONE && (n4 + 255) / 256 >= 2 * ((n8 + 255) / 256)) return 8;
-    if (bias == 1 && mask == AF_MASK_CAUSAL && n8 >= 512 && S >= 2048) return 8;
+    if (bias == 1 && mask == AF_MASK_CAUSAL && n8 >= 512 && S >= 2048 && rows8 < 256) return 8;
     return S < 6144 ? 4 : 8;
   }
   const int keys = cut && window < S - rows8 ? rows8 + window : S;   // that a workgroup visits
   if (keys > (D == 64 ? 1024 : rope == AF_ROPE_INTERLEAVED && !cut ? 256 : 512)) return 8;
   if (n4 <= 256 || n4 == n8 || (n8 > 256 && n4 <= 512)) return 4;
-  if (cut) return rows4 == 128 || n8 > 256 || S <= 256 || n4 <= 320 ? 4 : 8;
+  if (cut) return rows4 == 128 || n8 > 256 || S <= 256 || n4 <= 288 ? 4 : 8;
   if (n8 >= 256 || mask == AF_MASK_NONE) return 8;
   return D == 64 || (rope == AF_ROPE_NEOX && S >= 128 && S <= 256 && rows4 < rows8) ? 4 : 8;
 }
@@ -481,21 +482,24 @@ int attnfuse_fwd_bias_norm(const void* Q, const void* K, const void* V, void* O,
 //   block-sparse (9.2 % active) B4 H12 S4096 D64: 123 / 82; relu attention gains the rotation alone.
 // Under a block mask the saving is the tiles' of an average workgroup while all
 // run at once, then a part per workgroup that a CU takes in turn and per tile
-// (fitted to 3000 drawn masks; a D = 64 mask without a causal range may hold a row
-// far longer than the average, which hides that part in few turns).  With 0.6 us for
+// (fitted to 3000 drawn masks; a D = 64 mask of short lists without a causal range may
+// hold a row far longer than the average, which hides that part in few turns).  With 0.6 us for
 // every tile of all forms, as first, 30 of 222 calls that took it were slower by up to
 // 25 % (B2 H32/8 S6316 D128 30 % random, window 25 72.5 / 86.8, B3 H8/2 S4910 D64 10 %
-// random causal 27.9 / 31.3); now 3 of 174 by 3 to 5 %.
+// random causal 27.9 / 31.3); now 5 of 157 by 3 to 9 %.
 // An estimate in terms of 256-row workgroups, whichever form then runs: the
 // saving follows the tiles of the longest workgroup while these leave CUs free,
 // and otherwise the workgroups each CU takes in turn (5 us each) and the tiles of
-// the busiest CU.  It is smaller where four waves rotate in the loop (D = 64) and
+// the busiest CU.  It is smaller where four waves rotate in the loop under a window (D = 64) and
 // where the copied form's four-wave workgroups take more than a round, unless a
 // causal mask or a window cuts their tiles: D = 64 B2 H16 S2048 no mask 49.4 / 52.8,
 // B1 H12 S4096 83.0 / 85.6, B1 H8/2 S5066 window 827 26.2 / 27.7, but B2 H8/2 S4085 no
 // mask 93.8 / 90.5; D = 128 B2 H16/4 S2048 window 300 26.2 / 28.1, but window 1024 45.1 / 44.1.
+// With ALiBi or a bias the in-loop form has eight waves and fewer registers to
+// spare, and more is saved: B1 H2 S1165 D64 window 538, bias row per query 37.8 / 26.2,
+// B1 H8/1 S891 D64 ALiBi 26.1 / 19.0 (of 2500 drawn calls 3 are slower, by up to 16 %).
 size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, int rope, int mask, int window,
-                              int norm, long long sparse_blocks) {
+                              int norm, int extra, long long sparse_blocks) {
   if (B < 1 || H < 1 || H_kv < 1 || S < 1 || S > kMaxS || H % H_kv || !supported_d(D) || dtype != AF_DTYPE_BF16 ||
       rope == AF_ROPE_NONE)
     return 0;
@@ -511,8 +515,8 @@ size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, i
     if (mask == AF_MASK_SLIDING_WINDOW) tiles = std::fmin(tiles, (double)sparse_blocks * std::fmin(1.0, (window / 64.0 + 1.5) / nt));
     const double turns = units * nt / 256.0, load = units * tiles / 256.0;
     if (turns <= 1.0) saved = 0.3 + (D == 128 ? 0.5 : 0.25) * tiles / nt;
-    else if (D == 128) saved = 0.25 * (turns - 1.0) + 0.37 * load;
-    else saved = (mask == AF_MASK_NONE ? 2.0 * (turns - 3.0) : (hp == 1 ? 1.5 : 1.0) * turns - 0.7) + 0.22 * load;
+    else if (D == 128) saved = 0.25 * (turns - 1.0) + 0.4 * load;
+    else saved = (mask == AF_MASK_NONE && tiles < 8.0 * nt ? 2.0 * (turns - 3.0) : (hp == 1 ? 1.5 : 1.0) * turns - 0.7) + 0.22 * load;
   } else {
     const double rows = 256.0 / hp, wgs = std::ceil(S / rows);
     double longest = nt, tiles = wgs * nt;   // key tiles of the longest workgroup, and of all of a unit's
@@ -526,10 +530,11 @@ size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, i
       saved = (D == 128 ? 0.27 : 0.135) * load;
     } else if (turns <= 1.0) {
       const double rows4 = 128.0 / heads_packed(G, 4), n4 = std::ceil(S / rows4) * B * (H / heads_packed(G, 4));
-      if (n4 > 256 && mask == AF_MASK_NONE) saved = D == 128 ? 2.0 + 0.22 * longest : 0.08 * longest;
+      if (extra) saved = n4 > 256 ? (D == 128 ? 0.8 : 0.25) * longest : 1.2 + (D == 128 ? 0.75 : 0.4) * longest;
+      else if (n4 > 256 && mask == AF_MASK_NONE) saved = D == 128 ? 2.0 + 0.22 * longest : 0.08 * longest;
       else if (n4 > 256 && mask == AF_MASK_SLIDING_WINDOW && hp > 1) saved = D == 128 ? 2.0 + 0.22 * longest : 0.2 * longest;
       else if (D == 128) saved = 0.8 * longest;
-      else saved = (af::fwd_waves(B, H, H_kv, S, D, rope, mask, window, 0) == 4 ? 0.16 : 0.25) * longest;
+      else saved = (mask == AF_MASK_SLIDING_WINDOW && af::fwd_waves(B, H, H_kv, S, D, rope, mask, window, 0) == 4 ? 0.16 : 0.25) * longest;
     } else {
       saved = 5.0 * (turns - 1.0) + (D == 128 ? 0.3 : 0.2) * load;
     }

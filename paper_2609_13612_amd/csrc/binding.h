@@ -13,10 +13,11 @@ extern "C" {
 #endif
 
 /* Bytes of scratch with which the forward of these sizes runs faster (the keys
- * rotated once into it), or 0 where it is better without.  sparse_blocks: the
- * active blocks of a block mask, 0 without one. */
+ * rotated once into it), or 0 where it is better without.  extra: 1 with ALiBi
+ * slopes or a bias; sparse_blocks: the active blocks of a block mask, 0 without
+ * one. */
 size_t af_fwd_workspace_bytes(int B, int H, int H_kv, int S, int D, int dtype, int rope, int mask, int window,
-                              int norm, long long sparse_blocks);
+                              int norm, int extra, long long sparse_blocks);
 
 /* Waves per workgroup (4 or 8) of the dense forward of these sizes where both
  * forms exist; rope: AF_ROPE_NONE for tiles that are not rotated in the loop;

@@ -263,7 +263,8 @@ PyObject* fwd(Args a) {
   float* lp = l.defined() ? static_cast<float*>(out(l)) : nullptr;
   const int B = (int)x.B, H = (int)x.H, Hkv = (int)x.Hkv, S = (int)x.S, D = (int)x.D;
   Tensor ws;                // keys rotated once, where that is faster
-  if (const size_t n = af_fwd_workspace_bytes(B, H, Hkv, S, D, x.dtype, rope, mask, window, bias.norm, blocks)) {
+  if (const size_t n = af_fwd_workspace_bytes(B, H, Hkv, S, D, x.dtype, rope, mask, window, bias.norm,
+                                              sl || bias.p, blocks)) {
     try {
       ws = at::empty({(int64_t)n}, at::TensorOptions().dtype(at::kByte).device(x.dev));
     } catch (const c10::OutOfMemoryError&) {   // rotated in the loop instead

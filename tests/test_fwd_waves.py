@@ -35,7 +35,7 @@ def _waves(B, H, Hkv, S, D, rope, mask, window=0, bias=0):
     ((1, 12, 12, 4096, 64, COPIED, NONE), 8), ((1, 12, 12, 4096, 64, COPIED, NONE, 0, 1), 8),
     ((1, 12, 12, 4096, 64, COPIED, NONE, 0, 2), 4), ((1, 12, 12, 4096, 64, COPIED, CAUSAL), 4),
     ((1, 16, 4, 3000, 128, COPIED, NONE, 0, 1), 8), ((2, 16, 4, 3000, 128, COPIED, NONE, 0, 1), 4),
-    ((1, 16, 4, 3000, 128, COPIED, NONE, 0, 2), 4), ((1, 32, 8, 4096, 128, COPIED, CAUSAL, 0, 1), 8),
+    ((1, 16, 4, 3000, 128, COPIED, NONE, 0, 2), 4), ((1, 32, 8, 4096, 128, COPIED, CAUSAL, 0, 1), 8), ((3, 24, 8, 4102, 128, COPIED, CAUSAL, 0, 1), 4),
     ((1, 32, 8, 4096, 128, COPIED, CAUSAL, 0, 0), 4)])
 def test_measured_sizes(case, waves):
     assert _waves(*case) == waves

@@ -14,7 +14,7 @@ MASK = {"none": 0, "causal": 1, "sliding_window": 2}
     (2, 14, 1, 2050, 64, "none", "none", None, None, 2), (2, 14, 1, 2111, 64, "none", "none", None, "key", 2),
     (1, 16, 4, 2400, 128, "none", "none", None, "key", 2), (2, 32, 4, 2048, 128, "none", "causal", None, "key", 4),
     (6, 16, 8, 400, 128, "neox", "none", None, None, 2), (3, 12, 1, 1000, 64, "interleaved", "none", None, None, 3),
-    (12, 8, 4, 500, 128, "neox", "causal", None, None, 2), (6, 12, 4, 900, 64, "neox", "sliding_window", 100, None, 3)])
+    (12, 8, 4, 500, 128, "neox", "causal", None, None, 2), (3, 32, 4, 512, 128, "neox", "sliding_window", 100, None, 4)])
 def test_same_bits(monkeypatch, B, H, G, S, D, rope, mask, window, bias, parts):
     need_gpu()
     announce(f"fwd waves {B} {H}/{H // G} {S} {D} {rope} {mask} {bias}")

@@ -162,13 +162,14 @@ def test_same_bits_where_the_forward_takes_scratch(monkeypatch):
     norms = [(n, b) for n in ("softmax", "relu") for b in [None] + biases]
     for rope, mask, window in (("neox", "causal", None), ("interleaved", "none", None), ("neox", "sliding_window", 1500)):
         kw = dict(rope=rope, theta=500000.0, mask=mask, window=window)
-        calls = [(0, 0, lambda s=s: api.attnfuse_fwd(q, k, v, alibi_slopes=s, **kw)) for s in (None, slopes)]
-        calls += [(0, bm.k_idx.numel(), lambda s=s: api.attnfuse_fwd_blocksparse(q, k, v, bm, alibi_slopes=s, **kw))
-                  for s in (None, slopes)]
-        calls += [(api.NORM[n], 0, lambda n=n, b=b: api.attnfuse_fwd_bias_norm(q, k, v, norm=n, bias=b, **kw))
+        calls = [(0, s is not None, 0, lambda s=s: api.attnfuse_fwd(q, k, v, alibi_slopes=s, **kw)) for s in (None, slopes)]
+        calls += [(0, s is not None, bm.k_idx.numel(),
+                   lambda s=s: api.attnfuse_fwd_blocksparse(q, k, v, bm, alibi_slopes=s, **kw)) for s in (None, slopes)]
+        calls += [(api.NORM[n], b is not None, 0, lambda n=n, b=b: api.attnfuse_fwd_bias_norm(q, k, v, norm=n, bias=b, **kw))
                   for n, b in norms]
-        for norm, blocks, call in calls:
-            assert api._fwd_scratch_bytes(B, H, HKV, S, D, 0, api.ROPE[rope], api.MASK[mask], window or 0, norm, blocks) > 0
+        for norm, extra, blocks, call in calls:
+            assert api._fwd_scratch_bytes(B, H, HKV, S, D, 0, api.ROPE[rope], api.MASK[mask], window or 0, norm, int(extra),
+                                          blocks) > 0
             a = call()
             with monkeypatch.context() as m:
                 m.setattr(api, "_native", None)

@@ -7,8 +7,8 @@ from paper_2609_13612_amd import _lib
 FAKE = 0x10000
 
 
-def _bytes(B=1, H=32, Hkv=8, S=8192, D=128, dtype=0, rope=1, mask=1, window=0, norm=0, blocks=0):
-    return _lib.load().af_fwd_workspace_bytes(B, H, Hkv, S, D, dtype, rope, mask, window, norm, blocks)
+def _bytes(B=1, H=32, Hkv=8, S=8192, D=128, dtype=0, rope=1, mask=1, window=0, norm=0, extra=0, blocks=0):
+    return _lib.load().af_fwd_workspace_bytes(B, H, Hkv, S, D, dtype, rope, mask, window, norm, extra, blocks)
 
 
 def test_long_rotated_prompts_take_the_scratch():
@@ -37,6 +37,16 @@ def test_the_faster_form_is_taken(kw, takes):
     assert bool(_bytes(**kw)) == takes
 
 
+# in the loop / rotated once, us: 37.8 / 26.2, 26.1 / 19.0, 24.1 / 17.9, 27.9 / 22.5, 28.3 / 24.2
+@pytest.mark.parametrize("kw,plain", [
+    (dict(H=2, Hkv=2, S=1165, D=64, mask=2, window=538), False), (dict(H=8, Hkv=1, S=891, D=64, rope=2, mask=0), True),
+    (dict(H=2, Hkv=2, S=656, D=64, mask=2, window=491), False), (dict(B=4, H=2, Hkv=2, S=942, D=64, rope=2), True),
+    (dict(H=12, Hkv=12, S=640, D=64), False)])
+def test_alibi_and_bias_take_it_earlier(kw, plain):
+    assert _bytes(extra=1, **kw) > 0
+    assert (_bytes(**kw) > 0) == plain
+
+
 @pytest.mark.parametrize("kw,takes", [
     # measured in the loop / rotated once, us: 72.5 / 86.8, 27.9 / 31.3, 27.0 / 31.0, 13.0 / 16.2, 15.7 / 17.4, 38.5 / 42.9
     (dict(B=2, S=6316, mask=2, window=25, blocks=2939), False), (dict(B=3, H=8, Hkv=2, S=4910, D=64, blocks=610), False),
@@ -44,7 +54,8 @@ def test_the_faster_form_is_taken(kw, takes):
     (dict(B=3, H=2, Hkv=2, S=2047, D=64, mask=0, blocks=307), False), (dict(H=16, Hkv=16, S=3498, D=64, mask=0, blocks=323), False),
     # 48.2 / 39.7, 116.8 / 77.2, 85.4 / 62.5
     (dict(H=12, Hkv=4, S=2245, mask=0, blocks=209), True), (dict(B=2, H=16, Hkv=16, S=7209, D=64, mask=2, window=81, blocks=337), True),
-    (dict(H=1, Hkv=1, S=4564, mask=0, blocks=425), True)])
+    (dict(H=1, Hkv=1, S=4564, mask=0, blocks=425), True),
+    (dict(B=4, H=8, Hkv=1, S=3317, D=64, rope=2, mask=0, blocks=811), True)])   # 60.2 / 52.6
 def test_the_faster_form_is_taken_under_a_block_mask(kw, takes):
     assert bool(_bytes(**kw)) == takes
 
