@@ -39,7 +39,7 @@ Alongside, on the same inputs and outside the timed steps:
   counters;
 * the fp64 CPU oracle timed on a bounded sample (cpu_baseline).
 
-roofline.traffic is the forward kernel's measured HBM bytes per launch,
+roofline.traffic is the forward call's measured HBM bytes (both launches),
 taken from profiles/fwd_llama3_8b_hbm_traffic.json, which records the hash of
 the kernel sources it was measured on; if the sources differ, it is null.
 
@@ -78,7 +78,7 @@ def fwd_source_hash():
 
 
 def measured_traffic(workload):
-    """HBM bytes per fused-forward launch from the committed counter summary, if current."""
+    """HBM bytes per fused forward call from the committed counter summary, if current."""
     try:
         with open(TRAFFIC_FILE) as f:
             rec = json.load(f)
